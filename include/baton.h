@@ -379,8 +379,8 @@ baton_status baton_set_split_tokens(baton_cache* cache, int32_t tokens);
  * decode step's batch) on the library's weight-streaming kernel, which reads
  * the weight in a packed form made once per weight by baton_linear_pack.  The
  * weight dominates the traffic of such a product and is read about once from
- * HBM (rows past 64 are taken in chunks of 64 by workgroups dealt to the same
- * XCD one after the other, the later chunks finding the weight in that XCD's
+ * HBM (past 128 rows they are taken in two chunks by workgroups dealt to the
+ * same XCD one after the other, the second finding the weight in that XCD's
  * L2); the packed form lets each wave stream it in contiguous 1 KB blocks.
  *
  * baton_linear_packed_bytes: bytes of the packed form of an [out_dim][in_dim]

@@ -175,6 +175,42 @@ def test_linear_packed_silu(rows, F, in_dim):
     g0.close()
 
 
+# The products' kernels at the edges of their ranges and tiles: 1 and 8 rows
+# (the kernel without staging), 9 and 64 (staged rows), 65 .. 256 (one to two
+# chunks of five to eight row tiles), k of one 16-byte piece, of an odd number
+# of 32-wide blocks and with a tail shorter than 32, outputs that leave part of
+# a slice, of a wave's slices and of a workgroup empty, with and without splits
+# along k.  The rows of x past the last one and the outputs past the last row
+# are NaN: neither may be read into a result or written.
+@pytest.mark.parametrize("in_dim,out_dim,ws", [(8, 32, 0), (72, 96, 32 << 20), (200, 1056, 32 << 20),
+                                               (2056, 416, 32 << 20), (4104, 32, 32 << 20)])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 16, 33, 64, 65, 80, 81, 112, 128, 129, 161, 192, 225, 256])
+def test_packed_products_edges(rows, in_dim, out_dim, ws):
+    rng = np.random.default_rng(rows * 131 + in_dim + out_dim)
+    k = round(np.log2(in_dim) / 2)
+    xb, wb = _bits(rng, (rows, in_dim)), _bits(rng, (out_dim, in_dim), k)
+    g = PL.Gemm(ws_bytes=ws)
+    wp = g.pack(_dev(wb))
+    nan = lambda n: torch.full((rows + 16, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    xp, yp, ap = nan(in_dim), nan(out_dim), nan(out_dim // 2)
+    xp[:rows] = _dev(xb)
+    g.linear_packed(xp[:rows], wp, yp[:rows])
+    g.linear_packed_silu(xp[:rows], wp, ap[:rows])
+    y2 = yp.clone()
+    g.linear_packed(xp[:rows], wp, y2[:rows], accumulate=True)
+    torch.cuda.synchronize()
+    want = LL.linear(O.widen(xb, O.BF16), O.widen(wb, O.BF16))
+    _close(_val(yp[:rows].contiguous()), want, what="linear_packed")
+    _close(_val(y2[:rows].contiguous()), _val(yp[:rows].contiguous()) + want, what="accumulate")
+    F = out_dim // 2
+    # gate and up are rounded to bf16 before the activation: half a unit of each
+    # (2^-9) and of the result, and the activation's slope (at most 1.1 times |gate|'s)
+    _close(_val(ap[:rows].contiguous()), LL.silu(want[:, :F]) * want[:, F:], rel=2.0 ** -6, atol=4e-3, what="gated")
+    for t in (yp, y2, ap):
+        assert torch.isnan(t[rows:]).all(), "written past the last row"
+    g.close()
+
+
 def test_rmsnorm_and_silu_mul():
     rng = np.random.default_rng(11)
     xb, gb = _bits(rng, (7, 4096)), _bits(rng, (4096,))
