@@ -24,10 +24,6 @@
 #define BATON_MFMA_MIN_GROUP 2   // smallest q-heads per kv-head that takes the matrix-core kernel
 #endif
 
-#ifndef BATON_PREFILL_MFMA
-#define BATON_PREFILL_MFMA 1   // bf16 prefill attention on the matrix cores (0: vector ALUs)
-#endif
-
 #ifndef BATON_PREFILL_SPLIT_LEN
 #define BATON_PREFILL_SPLIT_LEN 256   // longer prompts: two key streams per prefill workgroup
 #endif
@@ -216,37 +212,53 @@ baton_status launch_segs(const baton_cache* c, const std::vector<Seg>& segs, hip
   }
 }
 
-template <int D, int G>
-void launch_prefill_g(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s) {
-  const bool fa = BATON_PREFILL_MFMA && c->d.dtype == BATON_BF16;
-  const int32_t per_tile = fa ? baton::kPrefillTile : baton::kWave / (D * c->esz / 16);
+// Tiles of per_tile positions over the prefilled queries, and how the heads
+// are dealt to the XCDs.
+void prefill_tiles(const baton_cache* c, baton::PrefillArgs& a, int32_t per_tile) {
   int32_t tiles = 0;
   for (int32_t i = 0; i < a.n_ins; ++i) {
     tiles += (a.plen[i] + per_tile - 1) / per_tile;
     a.tile_end[i] = tiles;
   }
-  const int32_t hq = c->d.n_kv_heads * G;
+  const int32_t hq = c->d.n_q_heads;
   a.n_tiles = tiles;
   a.n_attn = tiles * hq;
   // one XCD per kv-head's readers when the kv-heads (else the query heads) split evenly
-  a.unit_heads = c->d.n_kv_heads % 8 == 0 ? G : 1;
+  a.unit_heads = c->d.n_kv_heads % 8 == 0 ? c->group : 1;
   a.xcd_map = (hq / a.unit_heads) % 8 == 0 ? 1 : 0;
-  const dim3 grid((unsigned)((int64_t)tiles * hq));
-  const dim3 grid_fa((unsigned)((int64_t)tiles * (hq + c->d.n_kv_heads)));   // and the append workgroups
+}
+
+template <int D, int G>
+void launch_prefill_g(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s) {
+  prefill_tiles(c, a, baton::kPrefillTile);
+  const dim3 grid((unsigned)((int64_t)a.n_tiles * (c->d.n_q_heads + c->d.n_kv_heads)));   // and the append workgroups
   int32_t longest = 0;
   for (int32_t i = 0; i < a.n_ins; ++i) longest = std::max(longest, a.plen[i]);
-  if (fa && longest > BATON_PREFILL_SPLIT_LEN)
-    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 2>), grid_fa, dim3(512), 0, s, a);
-  else if (fa)
-    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 1>), grid_fa, dim3(256), 0, s, a);
-  else if (c->d.dtype == BATON_BF16)
-    hipLaunchKernelGGL((baton::prefill_valu_kernel<baton::BF16Tag, D, G>), grid, dim3(baton::kWave), 0, s, a);
+  if (longest > BATON_PREFILL_SPLIT_LEN)
+    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 2>), grid, dim3(512), 0, s, a);
   else
-    hipLaunchKernelGGL((baton::prefill_valu_kernel<baton::F32Tag, D, G>), grid, dim3(baton::kWave), 0, s, a);
+    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 1>), grid, dim3(256), 0, s, a);
+}
+
+template <int D>
+void launch_prefill_f32(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s) {
+  // 32 positions per workgroup where 16 would give more workgroups than run at
+  // once (by the kernel's registers four a CU at head_dim 64, two at 128);
+  // below that 16 shorten the launch.  16 / 32 positions, us: 8 heads of 64,
+  // 1024 tokens (512 workgroups) 27 / 35; 32 heads of 128, 300 tokens (608)
+  // 28 / 26, 1024 tokens (2048) 156 / 137.
+  prefill_tiles(c, a, 16);
+  if (a.n_attn > 256 * (D == 64 ? 4 : 2)) {
+    prefill_tiles(c, a, 32);
+    hipLaunchKernelGGL((baton::prefill_f32_kernel<D, 2>), dim3(a.n_attn), dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((baton::prefill_f32_kernel<D, 1>), dim3(a.n_attn), dim3(256), 0, s, a);
+  }
 }
 
 template <int D>
 void launch_prefill_d(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s) {
+  if (c->d.dtype == BATON_F32) return launch_prefill_f32<D>(c, a, s);
   switch (c->group) {
     case 1: launch_prefill_g<D, 1>(c, a, s); break;
     case 2: launch_prefill_g<D, 2>(c, a, s); break;

@@ -14,8 +14,8 @@
 // their own, one per (tile, kv-head), after all the attention workgroups in
 // the grid of prefill_fa_kernel (bf16, on the matrix cores): short ones, they
 // fill the end of the launch instead of lengthening every attention
-// workgroup by a load and a store of its tile; in prefill_valu_kernel (fp32,
-// the vector ALUs) the first query head of each kv-head appends its tile.
+// workgroup by a load and a store of its tile; in prefill_f32_kernel (fp32)
+// the first query head of each kv-head appends its tile.
 #pragma once
 
 #include "common.hpp"
@@ -93,66 +93,236 @@ __device__ __forceinline__ void prefill_append(const PrefillArgs& a, int b, int 
   }
 }
 
-// Any element type on the vector ALUs: a prompt position per lane group (LPT
-// lanes, 16 bytes each), TPI positions per wave, the keys one at a time.
-template <typename T, int D, int G>
-__global__ void __launch_bounds__(kWave) prefill_valu_kernel(const PrefillArgs a) {
-  using Geo = Geometry<T, D>;
-  constexpr int EPL = Geo::kEpl, LPT = Geo::kLpt, TPI = Geo::kTpi, VPT = Geo::kVpt;
-  const int lane = threadIdx.x;
-  const int r = lane / LPT, cl = lane % LPT;
+// fp32, on the fp32 matrix operation (v_mfma_f32_16x16x4_f32: fp32 products
+// and sums, so the same precision as the vector ALUs).  A workgroup of four
+// waves takes 16 QG positions of one query head; wave w takes every fourth
+// block of 16 keys from block w on, and the waves' softmax states merge through
+// LDS at the end.  What bounds it is, for short prompts, the chain of blocks a
+// wave walks -- hence the split of the keys over the waves instead of the
+// positions, and no barrier on the way -- and for long ones the loads of K in
+// the operand's layout (16 rows of 64 bytes, a quarter of the L1's rate), which
+// QG = 2 halves per matrix operation.
+//  * QK^T: A = 16 key rows, B = 16 positions.  The contraction's order is free,
+//    so step (i, e) takes element e of the 16-byte vectors at 16 i + 4 (l / 16):
+//    both operands are loaded 16 bytes per lane.  Lane l, register r holds the
+//    score of key 4 (l / 16) + r for position l % 16.
+//  * PV, transposed: O^T = V^T P^T.  Step r takes keys 4 (l / 16) + r, so B is
+//    the lane's own weight r; A = V^T of those keys, where tile (h, e) covers
+//    the columns 64 h + 4 c + e, c < 16: the V rows are loaded whole, 16 bytes
+//    per lane.  Lane l holds columns 64 h + 16 (l / 16) + 4 r + e of position
+//    l % 16: its outputs are 16-byte vectors over e.
+// One prompt, 8 query heads over 4 kv-heads, head_dim 64, us, against a kernel
+// that walked the keys one at a time on the vector ALUs: 40 tokens 16.4 -> 5.4, 300
+// 103.5 -> 9.8, 1024 359 -> 27; 32 heads of 128: 300 tokens 111 -> 26, 1024
+// 652 -> 137 (63 TFLOP/s of the matrix operation's 157).
+template <int D, int QG>
+__global__ void __launch_bounds__(256) prefill_f32_kernel(const PrefillArgs a) {
+  constexpr int VPT = D / 4, DI = D / 16, DH = D / 64, NW = 4;
+  __shared__ __attribute__((aligned(16))) f32x4 so[NW][DH * 4][kWave];
+  __shared__ float sm[NW][16], sl[NW][16];
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid % kWave, g4 = lane / 16, c16 = lane % 16;
   int hq;
   int32_t ins, tile;
   prefill_work(a, hq, ins, tile);
-  const int h = hq / G;
+  const int nkv = a.n_kv_heads, nq = a.n_attn / a.n_tiles, group = nq / nkv, h = hq / group;
   const int b = a.slot[ins];
   const int32_t p = a.plen[ins];
-  const int32_t i0 = tile * TPI;
+  const int32_t i0 = tile * 16 * QG;
   const int64_t row0 = (int64_t)b * a.T + (a.T - p);
-  const int nkv = a.n_kv_heads, nq = nkv * G;
   const u32x4* kin = reinterpret_cast<const u32x4*>(a.knew);
   const u32x4* vin = reinterpret_cast<const u32x4*>(a.vnew);
 
-  const int32_t qi = i0 + r;                           // this lane group's position
-  float qf[EPL];
-  {
-    const u32x4 w = qi < p ? reinterpret_cast<const u32x4*>(a.q)[((row0 + qi) * nq + hq) * VPT + cl]
-                           : u32x4{0, 0, 0, 0};
-    Lane16<T>::widen(w, qf);
+  // The positions as B operands, pre-scaled; positions past the prompt: zeros.
+  f32x4 qf[QG][DI];
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) qf[e] *= a.qscale;
-  }
-  float m = -INFINITY, l = 0.f, acc[EPL];
+  for (int gq = 0; gq < QG; ++gq) {
+    const int32_t qi = i0 + 16 * gq + c16;
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  const int32_t last = min(i0 + TPI - 1, p - 1);
-  for (int32_t t = 0; t <= last; ++t) {
-    const int64_t src = ((row0 + t) * nkv + h) * VPT + cl;
-    float kf[EPL], vf[EPL];
-    Lane16<T>::widen(kin[src], kf);
-    Lane16<T>::widen(vin[src], vf);
-    float d = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) d = fmaf(qf[e], kf[e], d);
-    d = group_sum<LPT>(d);
-    if (t <= qi) {
-      const float mn = fmaxf(m, d);
-      const float alpha = exp2f(m - mn);   // m = -inf at the first key: 0
-      const float pw = exp2f(d - mn);
-      l = l * alpha + pw;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(pw, vf[e], acc[e] * alpha);
-      m = mn;
+    for (int i = 0; i < DI; ++i) {
+      const u32x4 x = qi < p ? reinterpret_cast<const u32x4*>(a.q)[((row0 + qi) * nq + hq) * VPT + 4 * i + g4]
+                             : u32x4{0, 0, 0, 0};
+      qf[gq][i] = __builtin_bit_cast(f32x4, x) * a.qscale;
     }
   }
-  if (qi < p) {
-    const float inv = 1.f / l;
-    float o[EPL];
+  float m[QG], l[QG];
+  f32x4 o[QG][DH][4];
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) o[e] = acc[e] * inv;
-    reinterpret_cast<u32x4*>(a.out)[((row0 + qi) * nq + hq) * VPT + cl] = Lane16<T>::narrow(o);
+  for (int gq = 0; gq < QG; ++gq) {
+    m[gq] = -INFINITY;
+    l[gq] = 0.f;
+#pragma unroll
+    for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[gq][hh][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (hq % G == 0) prefill_append<VPT>(a, b, h, p, row0, i0, min(TPI, p - i0), lane);
+  // The prompt's keys and values of head h as raw buffers; a token past the
+  // prompt gets an offset beyond the range, which loads zeros.
+  const uint32_t tok_bytes = (uint32_t)nkv * VPT * 16;
+  const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<u32x4*>(kin + (row0 * nkv + h) * VPT), 0, (uint32_t)p * tok_bytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<u32x4*>(vin + (row0 * nkv + h) * VPT), 0, (uint32_t)p * tok_bytes, kBufferWord3);
+  auto load = [](__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+  };
+  f32x4 kf[DI], vf[4][DH];
+  auto load_k = [&](int32_t kb) {
+    const int32_t t = kb + c16;
+    const uint32_t off = t < p ? (uint32_t)t * tok_bytes + 16u * g4 : 0x80000000u;
+#pragma unroll
+    for (int i = 0; i < DI; ++i) kf[i] = load(rk, off + 64u * i);
+  };
+  auto load_v = [&](int32_t kb) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int32_t t = kb + 4 * g4 + r;
+      const uint32_t off = t < p ? (uint32_t)t * tok_bytes + 16u * c16 : 0x80000000u;
+#pragma unroll
+      for (int hh = 0; hh < DH; ++hh) vf[r][hh] = load(rv, off + 256u * hh);
+    }
+  };
+  const int32_t last = min(i0 + 16 * QG, p) - 1;   // the last position, and the last key it sees
+  int32_t kb = 16 * w;
+  if (kb <= last) {
+    load_k(kb);
+    load_v(kb);
+  }
+  for (; kb <= last; kb += 16 * NW) {               // wave-uniform
+    // Partial sums over four vectors each (by element, and by halves at
+    // head_dim 128), added as a tree: chains as short in rounding as a lane's
+    // own sum of four on the vector ALUs, and short in latency.
+    constexpr int NP = DI;                          // 4 (head_dim 64) or 8
+    f32x4 sp[QG][NP], s[QG];
+#pragma unroll
+    for (int gq = 0; gq < QG; ++gq)
+#pragma unroll
+      for (int e = 0; e < NP; ++e) sp[gq][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < DI; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int gq = 0; gq < QG; ++gq)
+          sp[gq][(4 * i + e) % NP] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][e], qf[gq][i][e], sp[gq][(4 * i + e) % NP], 0, 0, 0);
+#pragma unroll
+    for (int gq = 0; gq < QG; ++gq) {
+#pragma unroll
+      for (int n = NP / 2; n > 0; n /= 2)
+#pragma unroll
+        for (int e = 0; e < n; ++e) sp[gq][e] += sp[gq][e + n];
+      s[gq] = sp[gq][0];
+    }
+    const bool more = kb + 16 * NW <= last;
+    if (more) load_k(kb + 16 * NW);
+#pragma unroll
+    for (int gq = 0; gq < QG; ++gq) {
+      const int32_t qi = i0 + 16 * gq + c16;
+      if (kb + 15 > i0 + 16 * gq) {                 // some position does not see the whole block
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[gq][r] = kb + 4 * g4 + r <= qi ? s[gq][r] : -INFINITY;
+      }
+      const float mx = max_over_groups(fmaxf(fmaxf(s[gq][0], s[gq][1]), fmaxf(s[gq][2], s[gq][3])));
+      const float mn = fmaxf(m[gq], mx);
+      const float ref = mn == -INFINITY ? 0.f : mn;
+      const float alpha = exp2f(m[gq] - ref);       // m = -inf before the first visible key: 0
+      float sum = 0.f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        s[gq][r] = exp2f(s[gq][r] - ref);
+        sum += s[gq][r];
+      }
+      l[gq] = l[gq] * alpha + sum;                  // this lane's keys
+      m[gq] = mn;
+#pragma unroll
+      for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[gq][hh][e] *= alpha;
+    }
+    // A weight of 0 does not hide a value that is not finite: where a position
+    // may not see the whole block and some value of it is inf or NaN (rare),
+    // each position adds its visible keys' values one by one.
+    bool odd = false;
+    if (kb + 15 > i0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) odd = odd || (__float_as_uint(vf[r][hh][e]) & 0x7F800000u) == 0x7F800000u;
+    }
+    if (__ballot(odd)) {
+#pragma unroll
+      for (int gq = 0; gq < QG; ++gq)
+        for (int j = 0; j < 16 && kb + j <= last; ++j) {
+          // key j's weight for position c16: register j % 4 of lane group j / 4
+          const float wj = __shfl(j % 4 == 0 ? s[gq][0] : j % 4 == 1 ? s[gq][1] : j % 4 == 2 ? s[gq][2] : s[gq][3],
+                                  16 * (j / 4) + c16, kWave);
+          if (kb + j > i0 + 16 * gq + c16) continue;
+#pragma unroll
+          for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const f32x4 v = load(rv, (uint32_t)(kb + j) * tok_bytes + 256u * hh + 64u * g4 + 16u * r);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[gq][hh][e][r] = fmaf(wj, v[e], o[gq][hh][e][r]);
+            }
+        }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int gq = 0; gq < QG; ++gq)
+              o[gq][hh][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][hh][e], s[gq][r], o[gq][hh][e], 0, 0, 0);
+    }
+    if (more) load_v(kb + 16 * NW);
+  }
+  // Merge the waves, a position group at a time: wave w finishes the vectors
+  // of register r = w.
+#pragma unroll
+  for (int gq = 0; gq < QG; ++gq) {
+    if (gq > 0) __syncthreads();
+    const float lw = sum_over_groups(l[gq]);
+    if (g4 == 0) {
+      sm[w][c16] = m[gq];
+      sl[w][c16] = lw;
+    }
+#pragma unroll
+    for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        so[w][hh * 4 + r][lane] = f32x4{o[gq][hh][0][r], o[gq][hh][1][r], o[gq][hh][2][r], o[gq][hh][3][r]};
+    __syncthreads();
+    const int32_t qi = i0 + 16 * gq + c16;
+    float mm = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) mm = fmaxf(mm, sm[q][c16]);
+    float lt = 0.f, f[NW];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const float mq = sm[q][c16];
+      f[q] = mq == -INFINITY ? 0.f : exp2f(mq - mm);
+      lt += f[q] * sl[q][c16];
+    }
+    const float inv = 1.f / lt;
+    if (qi < p) {
+#pragma unroll
+      for (int hh = 0; hh < DH; ++hh) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < NW; ++q) v += so[q][hh * 4 + w][lane] * f[q];
+        v *= inv;
+        reinterpret_cast<f32x4*>(a.out)[((row0 + qi) * nq + hq) * VPT + 16 * hh + 4 * g4 + w] = v;
+      }
+    }
+  }
+  if (hq % group == 0) prefill_append<VPT>(a, b, h, p, row0, i0, min(16 * QG, p - i0), tid, 256);
 }
 
 // bf16 on the matrix cores, flash-attention style: a workgroup of 4*S waves

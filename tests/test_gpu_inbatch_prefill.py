@@ -190,3 +190,51 @@ def test_many_holes_rows_of_different_ages(shape):
             s += 1
     err = parity.run_script(shape, ops, capacity=2048, split=64)
     print(f"[inbatch many holes] {shape}: {s} steps, max abs error {err:.3g}", flush=True)
+
+
+# The fp32 prefill kernel at the edges of its tiles: prompts of one token, one
+# short of, exactly and one past a 16-key block and a round of the four waves'
+# blocks, several prompts in one step, and enough heads and tiles for 32
+# positions per workgroup (64 heads of 64 and 32 of 128 at 300 tokens); then
+# the same prompt with a value that is not finite near its end, which the
+# positions before it must not see.
+@pytest.mark.parametrize("heads,kv,D,lens", [(4, 4, 64, [1, 15, 16, 17]), (4, 2, 128, [63, 64, 65, 2]),
+                                             (8, 1, 64, [33, 130]), (64, 8, 64, [300]), (32, 32, 128, [300, 49])])
+def test_f32_prefill_edges(heads, kv, D, lens):
+    import torch
+    from paper_2410_18701_amd.cache import BatonCache
+    B, T = len(lens), max(lens)
+    g = torch.Generator().manual_seed(sum(lens) + heads)
+    q, k, v = (torch.randn((B, T, h, D), generator=g) for h in (heads, kv, kv))
+
+    def run(v):
+        cache = BatonCache(1, B, heads, kv, D, capacity=T + 64, dtype="f32")
+        cache.shape_insert(list(range(B)), lens)
+        out = torch.full((B, T, heads, D), float("nan"), device="cuda")
+        cache.decode_attn(0, q.cuda(), k.cuda(), v.cuda(), out=out)
+        cache.advance()
+        ks, vs = cache.extract(list(range(B)))
+        for b, p in enumerate(lens):
+            assert torch.equal(ks[b][0].cpu(), k[b, T - p:].transpose(0, 1).contiguous()), "appended keys"
+            assert torch.equal(vs[b][0].cpu().view(torch.int32),
+                               v[b, T - p:].transpose(0, 1).contiguous().view(torch.int32)), "appended values"
+        cache.close()
+        return out.cpu()
+
+    out = run(v)
+    for b, p in enumerate(lens):
+        assert torch.isnan(out[b, :T - p]).all(), "a position without a token was written"
+        hide = torch.ones(p, p, dtype=torch.bool).triu(1)
+        for h in range(heads):
+            kk, vv = (x[b, T - p:, h // (heads // kv)].double() for x in (k, v))
+            s = (q[b, T - p:, h].double() @ kk.T * D ** -0.5).masked_fill(hide, -np.inf)
+            err = (out[b, T - p:, h].double() - torch.softmax(s, -1) @ vv).abs().max()
+            assert err <= 1e-5, f"slot {b} head {h}: {err}"
+    for bad in (float("inf"), float("nan")):
+        vb = v.clone()
+        vb[:, T - 1] = bad
+        ob = run(vb)
+        for b, p in enumerate(lens):
+            rows = slice(T - p, T - 1)
+            assert (ob[b, rows] - out[b, rows]).abs().max() <= 1e-5 if p > 1 else True
+            assert not torch.isfinite(ob[b, T - 1]).any()
