@@ -225,6 +225,13 @@ def baton_cache_query(cache, batch):
     return L.value, base.value, list(lens)
 
 
+def baton_cache_length(cache):
+    """The padded length L alone (baton_cache_query without the other outputs)."""
+    L = ctypes.c_int64()
+    _check(lib().baton_cache_query(cache, ctypes.byref(L), None, None), "baton_cache_query")
+    return L.value
+
+
 def baton_set_split_tokens(cache, tokens):
     _check(lib().baton_set_split_tokens(cache, tokens), "baton_set_split_tokens")
 

@@ -8,11 +8,7 @@ output projection added to the residual stream -> RMS norm -> gate/up
 projection -> silu(gate) * up -> down projection added to the residual stream.
 """
 from . import baton as B
-
-
-def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+from .cache import _cur_stream as _stream
 
 
 class PackedWeight:

@@ -114,3 +114,14 @@ def test_decode_step_over_holey_rows_in_a_hip_graph(shape):
     del g
     eager.close()
     graphed.close()
+
+
+def test_calls_follow_the_current_stream():
+    """The calls without a stream argument go to torch's current stream, inside and
+    outside a stream context."""
+    from paper_2410_18701_amd.cache import _cur_stream
+    assert _cur_stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert _cur_stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert _cur_stream() == torch.cuda.current_stream().cuda_stream
