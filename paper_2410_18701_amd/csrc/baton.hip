@@ -230,14 +230,25 @@ void prefill_tiles(const baton_cache* c, baton::PrefillArgs& a, int32_t per_tile
 
 template <int D, int G>
 void launch_prefill_g(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s) {
-  prefill_tiles(c, a, baton::kPrefillTile);
-  const dim3 grid((unsigned)((int64_t)a.n_tiles * (c->d.n_q_heads + c->d.n_kv_heads)));   // and the append workgroups
   int32_t longest = 0;
   for (int32_t i = 0; i < a.n_ins; ++i) longest = std::max(longest, a.plen[i]);
+  auto grid = [&] { return dim3((unsigned)((int64_t)a.n_tiles * (c->d.n_q_heads + c->d.n_kv_heads))); };   // and the append workgroups
+  // 128 positions per workgroup and 32 per wave where that still gives two
+  // workgroups a CU and a prompt is long enough for its blocks to outweigh the
+  // longer chain of each.  64 / 128 positions, us per layer at head_dim 128:
+  // 64 heads, 4096 tokens 390 / 296, 2500 154 / 127, 1024 (512 workgroups) 41 /
+  // 36; 32 heads, 2048 tokens (512) 68 / 60, 1024 (256) 26 / 31; 64 heads, eight
+  // prompts of 512 91 / 76, four of 384 33 / 35, eight of 256 29 / 36.
+  prefill_tiles(c, a, baton::kPrefillTile32);
+  if (longest >= 512 && a.n_attn >= 512) {
+    hipLaunchKernelGGL((baton::prefill_fa32_kernel<D, G>), grid(), dim3(256), 0, s, a);
+    return;
+  }
+  prefill_tiles(c, a, baton::kPrefillTile);
   if (longest > BATON_PREFILL_SPLIT_LEN)
-    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 2>), grid, dim3(512), 0, s, a);
+    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 2>), grid(), dim3(512), 0, s, a);
   else
-    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 1>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((baton::prefill_fa_kernel<D, G, 1>), grid(), dim3(256), 0, s, a);
 }
 
 template <int D>

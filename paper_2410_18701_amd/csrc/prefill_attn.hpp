@@ -646,6 +646,233 @@ prefill_fa_kernel(const PrefillArgs a) {
   }
 }
 
+// bf16 for long prompts, on v_mfma_f32_32x32x16_bf16: four waves of 32 prompt
+// positions of one query head, the keys in blocks of 32.  In the kernel above
+// every 32 x 16 block of scores reads its 16 KB of keys and values from LDS (73%
+// of the LDS's rate at 4096 tokens); here the same 16 KB serve 32 positions, the
+// loads go to LDS without registers two blocks ahead, and the block loop is
+// pipelined in software so that a wave's matrix and vector work overlap:
+// iteration t multiplies the values of block t - 1 and takes the maximum of block
+// t's scores, then computes the scores of block t + 1 and the weights of block t.
+//  * scores: A = 32 key rows, B = 32 positions; lane l, register r: position
+//    l % 32, key 8 (r / 4) + 4 (l / 32) + r % 4.
+//  * values: O^T = V^T P^T; step j takes registers 8 j .. 8 j + 7 of the lane's
+//    own weights as B, so A's k = 8 (l / 32) + e stands for key 16 j + 4 (l / 32)
+//    + e (e < 4) and 16 j + 8 + 4 (l / 32) + e - 4: two transposing LDS loads.
+//  * the weights' sum is of the bf16 weights P.V is made of.
+// 64 query heads over 8 kv-heads of 128, 4096 tokens: 390 -> 296 us (0.70 -> 0.93
+// PFLOP/s over the visible pairs).  What bounds it now: two waves per SIMD (173
+// registers) that wait for their own chain a third of the time, and the clock,
+// about 1.9 GHz under this load; capped for three waves it spills, and two
+// accumulators per score or a raised wave priority changed nothing.
+constexpr int kPrefillTile32 = 128;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// LDS rows are filled by LDS-direct loads (no registers hold keys or values on
+// their way), so they cannot be padded; the 16-byte chunks of a row are placed
+// by the row instead, so that reads of many rows spread over all banks:
+//  * keys (a chunk of 32 rows per read, lane half hh reading chunk 2 kk + hh):
+//    the halves in different halves of the row, xor the row;
+//  * values (transposing loads, 64 bytes of 4 + 4 rows): 64-byte units xor the
+//    row.
+// (Chunks xor the row for both cost 60% of the LDS cycles in conflicts.)
+template <int CH>   // chunks per row: 16 (head_dim 128) or 8
+__device__ __forceinline__ int key_place(int chunk, int row) {
+  return ((chunk % 2) * (CH / 2) + chunk / 2) ^ (CH == 16 ? row % 16 : row / 2 % 8);
+}
+template <int CH>
+__device__ __forceinline__ int key_chunk(int place, int row) {   // the inverse in `chunk`
+  const int y = place ^ (CH == 16 ? row % 16 : row / 2 % 8);
+  return (y % (CH / 2)) * 2 + y / (CH / 2);
+}
+template <int CH>
+__device__ __forceinline__ int value_place(int chunk, int row) {   // its own inverse
+  return chunk ^ (4 * (CH == 16 ? row % 4 : row / 2 % 2));
+}
+__device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint8_t* dst, uint32_t off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  // lane l's 16 bytes land at dst + 16 l
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off, 0, 0, 0);
+#endif
+}
+
+template <int D, int G>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+prefill_fa32_kernel(const PrefillArgs a) {
+  constexpr int VPT = D / 8, KK = D / 16, DT = D / 32, TILE = kPrefillTile32;
+  constexpr int ROW = D * 2;
+  constexpr int RPI = kWave / VPT, NI = 32 / RPI / 4;   // rows per load; loads per wave and block
+  // a buffer each, not an array of three: reads of one must not wait for the loads into the other
+  __shared__ __attribute__((aligned(1024))) uint8_t ldsK0[32 * ROW], ldsK1[32 * ROW], ldsK2[32 * ROW];
+  __shared__ __attribute__((aligned(1024))) uint8_t ldsV0[32 * ROW], ldsV1[32 * ROW], ldsV2[32 * ROW];
+  const int tid = threadIdx.x;
+  if ((int32_t)blockIdx.x >= a.n_attn) {
+    const int32_t j = (int32_t)blockIdx.x - a.n_attn;
+    const int32_t g = j / a.n_kv_heads, h = j % a.n_kv_heads;
+    int32_t ins = 0;
+    while (ins < a.n_ins - 1 && g >= a.tile_end[ins]) ++ins;
+    const int32_t tile = a.tile_end[ins] - 1 - g, p = a.plen[ins], b = a.slot[ins];
+    const int64_t row0 = (int64_t)b * a.T + (a.T - p);
+    prefill_append<VPT>(a, b, h, p, row0, tile * TILE, min(TILE, p - tile * TILE), tid, 256);
+    return;
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
+  const int c32 = lane % 32, hh = lane / 32, g4 = lane / 16, m16 = lane % 16;
+  int hq;
+  int32_t ins, tile;
+  prefill_work(a, hq, ins, tile);
+  const int h = hq / G;
+  const int b = a.slot[ins];
+  const int32_t p = a.plen[ins];
+  const int32_t wg0 = tile * TILE, i0 = wg0 + 32 * wave;
+  const int64_t row0 = (int64_t)b * a.T + (a.T - p);
+  const int nkv = a.n_kv_heads, nq = nkv * G;
+  const u32x4* qin = reinterpret_cast<const u32x4*>(a.q);
+  const u32x4* kin = reinterpret_cast<const u32x4*>(a.knew);
+  const u32x4* vin = reinterpret_cast<const u32x4*>(a.vnew);
+  const float qscale = fabsf(a.qscale);
+  const uint32_t qsw = a.qscale < 0.f ? 0x80008000u : 0u;
+  const u32x4 qsign = {qsw, qsw, qsw, qsw};
+  const int32_t qi = i0 + c32;
+  bf16x8 qb[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk)
+    qb[kk] = as_bf16x8(qi < p ? qin[((row0 + qi) * nq + hq) * VPT + kk * 2 + hh] ^ qsign : u32x4{0, 0, 0, 0});
+
+  const uint32_t tok_bytes = (uint32_t)nkv * VPT * 16;
+  const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<u32x4*>(kin + (row0 * nkv + h) * VPT), 0, (uint32_t)p * tok_bytes, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<u32x4*>(vin + (row0 * nkv + h) * VPT), 0, (uint32_t)p * tok_bytes, kBufferWord3);
+  // Block t's rows into buf: load i of this wave brings rows (4 i + wave) RPI ..
+  const int lr = wave * RPI + lane / VPT;
+  uint32_t off_k[NI], off_v[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int row = 4 * RPI * i + lr;
+    off_k[i] = (uint32_t)row * tok_bytes + (uint32_t)key_chunk<VPT>(lane % VPT, row) * 16u;
+    off_v[i] = (uint32_t)row * tok_bytes + (uint32_t)value_place<VPT>(lane % VPT, row) * 16u;
+  }
+  auto fetch = [&](__amdgpu_buffer_rsrc_t r, const uint32_t (&off)[NI], int32_t t, uint8_t* buf) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      lds_load16(r, buf + (4 * i + wave) * 1024,
+                 32 * t + 4 * RPI * i < p - lr ? off[i] + (uint32_t)(32 * t) * tok_bytes : 0x80000000u);
+  };
+  const int k_off = c32 * ROW + key_place<VPT>(hh, c32) * 16;   // chunk 2 kk + hh: xor 16 kk
+  auto scores = [&](const uint8_t* buf) {
+    f32x16 s = {};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*reinterpret_cast<const u32x4*>(buf + (k_off ^ (16 * kk)))),
+                                                  qb[kk], s, 0, 0, 0);
+    return s;
+  };
+  // Transposing load (j, e, dt): key 16 j + 8 e + 4 hh + m / 4, columns 32 dt +
+  // 16 (g % 2) + 4 (m % 4), m = lane % 16, g = lane / 16.
+  const int v_row = 4 * hh + m16 / 4;              // key 16 j + 8 e more: the same place
+  const int v_off = v_row * ROW + value_place<VPT>(2 * (g4 % 2) + (m16 % 4) / 2, v_row) * 16 + 8 * (m16 % 2);
+
+  const int32_t last_t = (min(wg0 + TILE, p) - 1) / 32;                    // the workgroup's last block
+  const int32_t my_t = i0 < p ? (min(i0 + 32, p) - 1) / 32 : -1;           // this wave's
+  float m = -INFINITY, lsum = 0.f;
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x16{};
+  bf16x8 pw[2] = {as_bf16x8(u32x4{0, 0, 0, 0}), as_bf16x8(u32x4{0, 0, 0, 0})};   // weights of block t - 1
+
+  // Iteration t, with block t's scores in s: the loads of V block t + 1 and K
+  // block t + 3 go where V block t - 2 and K block t were last read before the
+  // barrier that began it; V block t - 1 and K block t + 1 are read.  Its
+  // barrier comes after every load but this iteration's own 2 NI (and every
+  // LDS read) of the wave has finished, so a load has two iterations.
+  f32x16 s;
+  auto step = [&](int32_t t, const uint8_t* kbuf, const uint8_t* vbuf, uint8_t* kfree, uint8_t* vfree) {
+    fetch(rv, off_v, t + 1, vfree);
+    fetch(rk, off_k, t + 3, kfree);
+    if (t <= my_t + 1) {                         // wave-uniform; iteration my_t + 1 only adds block my_t's values
+      if (32 * t + 31 > i0) {                    // not every position sees the whole block
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int32_t key = 32 * t + 8 * (r / 4) + 4 * hh + r % 4;
+          s[r] = key <= qi && qi < p ? s[r] : -INFINITY;
+        }
+      }
+      float mx = s[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+      if (t > 0) {                               // the values of block t - 1
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) {
+            s16x4 w2[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+              w2[e] = lds_read_tr16(vbuf + (16 * j + 8 * e) * ROW + (v_off ^ (64 * dt)));
+            o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w2), pw[j], o[dt], 0, 0, 0);
+          }
+      }
+      {
+        const uint32_t u = __float_as_uint(mx);
+        const auto x = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        mx = fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])) * qscale;
+      }
+      if (__ballot(mx > m + kPrefillLazy)) {     // the reference moves, as in the kernel above
+        const float mn = mx > m + kPrefillLazy ? mx : m;
+        const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+        lsum *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
+        m = mn;
+      }
+      const float ref = m == -INFINITY ? 0.f : m;
+      const f32x16 sn = scores(kbuf);            // of block t + 1, beside the weights of block t
+#pragma unroll
+      for (int r = 0; r < 16; ++r) pw[r / 8][r % 8] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[r], qscale, -ref));
+      const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3F803F80u);
+#pragma unroll
+      for (int r = 0; r < 16; r += 2)
+        lsum = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pw[r / 8][r % 8], pw[r / 8][r % 8 + 1]}, ones, lsum, false);
+      s = sn;
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (2 * NI));   // vmcnt <= 2 NI, lgkmcnt 0
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  fetch(rk, off_k, 0, ldsK0);
+  fetch(rk, off_k, 1, ldsK1);
+  fetch(rk, off_k, 2, ldsK2);
+  fetch(rv, off_v, 0, ldsV0);
+  __syncthreads();
+  s = scores(ldsK0);
+  __syncthreads();
+  for (int32_t t = 0;; t += 3) {                 // bounds are workgroup-uniform; iteration last_t + 1 is the last
+    step(t, ldsK1, ldsV2, ldsK0, ldsV1);
+    if (t > last_t) break;
+    step(t + 1, ldsK2, ldsV0, ldsK1, ldsV2);
+    if (t + 1 > last_t) break;
+    step(t + 2, ldsK0, ldsV1, ldsK2, ldsV0);
+    if (t + 2 > last_t) break;
+  }
+  {
+    const uint32_t u = __float_as_uint(lsum);
+    const auto x = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    lsum = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  }
+  if (qi < p) {
+    const float inv = 1.f / lsum;
+    uint16_t* o16 = reinterpret_cast<uint16_t*>(a.out) + ((row0 + qi) * nq + hq) * D + 4 * hh;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; r += 4)
+        *reinterpret_cast<uint2*>(o16 + 32 * dt + 2 * r) =
+            make_uint2(f32_to_bf16_rne(o[dt][r] * inv) | (f32_to_bf16_rne(o[dt][r + 1] * inv) << 16),
+                       f32_to_bf16_rne(o[dt][r + 2] * inv) | (f32_to_bf16_rne(o[dt][r + 3] * inv) << 16));
+  }
+}
+
 }  // namespace baton
-
-

@@ -238,3 +238,42 @@ def test_f32_prefill_edges(heads, kv, D, lens):
             rows = slice(T - p, T - 1)
             assert (ob[b, rows] - out[b, rows]).abs().max() <= 1e-5 if p > 1 else True
             assert not torch.isfinite(ob[b, T - 1]).any()
+
+
+# The long-prompt bf16 kernel (128 positions per workgroup; a prompt of 512 tokens
+# and more, 512 workgroups) at its edges: one token past and one short of a 32-key
+# block, a wave's positions and a tile, prompts of a few tokens beside a long one
+# (tiles of waves with nothing to do), every grouping, both head sizes, a negative
+# scale; against float64 on a few heads, the appended rows bit for bit on all.
+@pytest.mark.parametrize("heads,kv,D,lens,scale", [
+    (64, 8, 128, [1025, 1, 31], 0.0), (64, 64, 128, [927, 129], 0.0), (64, 16, 64, [513, 512, 127], 0.0),
+    (64, 32, 128, [1000, 33], -0.2), (64, 8, 64, [1030, 128, 2], 1.0)])
+def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
+    import torch
+    from paper_2410_18701_amd.cache import BatonCache
+    B, T = len(lens), max(lens)
+    g = torch.Generator().manual_seed(sum(lens) + heads)
+    q, k, v = (torch.randn((B, T, h, D), generator=g).bfloat16() for h in (heads, kv, kv))
+    for b, p in enumerate(lens):          # positions without a token: not read into a result
+        for x in (q, k, v):
+            x[b, :T - p] = float("nan")
+    assert sum(-(-p // 128) for p in lens) * heads >= 512
+    cache = BatonCache(1, B, heads, kv, D, capacity=T + 64, dtype="bf16")
+    cache.shape_insert(list(range(B)), lens)
+    out = torch.full((B, T, heads, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    cache.decode_attn(0, q.cuda(), k.cuda(), v.cuda(), out=out, scale=scale)
+    cache.advance()
+    ks, vs = cache.extract(list(range(B)))
+    out = out.cpu()
+    sc = scale or D ** -0.5
+    for b, p in enumerate(lens):
+        assert torch.equal(ks[b][0].cpu(), k[b, T - p:].transpose(0, 1).contiguous()), "appended keys"
+        assert torch.equal(vs[b][0].cpu(), v[b, T - p:].transpose(0, 1).contiguous()), "appended values"
+        assert torch.isnan(out[b, :T - p]).all(), "a position without a token was written"
+        hide = torch.ones(p, p, dtype=torch.bool).triu(1)
+        for h in (0, heads // 2 - 1, heads - 1):
+            kk, vv = (x[b, T - p:, h // (heads // kv)].double() for x in (k, v))
+            s = (q[b, T - p:, h].double() @ kk.T * sc).masked_fill(hide, -np.inf)
+            err = (out[b, T - p:, h].double() - torch.softmax(s, -1) @ vv).abs().max()
+            assert err <= 2e-2, f"slot {b} head {h}: {err}"
+    cache.close()
