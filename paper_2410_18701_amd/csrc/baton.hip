@@ -233,14 +233,17 @@ void launch_prefill_g(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s
   int32_t longest = 0;
   for (int32_t i = 0; i < a.n_ins; ++i) longest = std::max(longest, a.plen[i]);
   auto grid = [&] { return dim3((unsigned)((int64_t)a.n_tiles * (c->d.n_q_heads + c->d.n_kv_heads))); };   // and the append workgroups
-  // 128 positions per workgroup and 32 per wave where that still gives two
-  // workgroups a CU and a prompt is long enough for its blocks to outweigh the
-  // longer chain of each.  64 / 128 positions, us per layer at head_dim 128:
-  // 64 heads, 4096 tokens 390 / 296, 2500 154 / 127, 1024 (512 workgroups) 41 /
-  // 36; 32 heads, 2048 tokens (512) 68 / 60, 1024 (256) 26 / 31; 64 heads, eight
-  // prompts of 512 91 / 76, four of 384 33 / 35, eight of 256 29 / 36.
+  // 128 positions per workgroup and 32 per wave where there are enough
+  // workgroups of long enough prompts: the product of the two decides (its
+  // fewer, longer chains lose where the GPU is not full of them).  64 / 128
+  // positions, us per layer at head_dim 128: 64 heads, 4096 tokens (2048
+  // workgroups) 403 / 322, 2500 (1280) 160 / 140, eight prompts of 512 (2048) 90 /
+  // 82; 32 heads, 2048 tokens (512) 71 / 66, 1500 and 1200 (704) 66 / 60, two of
+  // 1024 (512) 44 / 46.  At head_dim 64 the 64-position kernel runs four
+  // workgroups a CU: 32 heads, 4096 tokens (1024) 117 / 102, 2048 (512) 38 / 39,
+  // four of 1024 (1024) 43 / 49.
   prefill_tiles(c, a, baton::kPrefillTile32);
-  if (longest >= 512 && a.n_attn >= 512) {
+  if (longest >= 512 && (int64_t)longest * a.n_attn >= (D == 64 ? 1 << 21 : 1 << 20)) {
     hipLaunchKernelGGL((baton::prefill_fa32_kernel<D, G>), grid(), dim3(256), 0, s, a);
     return;
   }

@@ -660,12 +660,20 @@ prefill_fa_kernel(const PrefillArgs a) {
 //    own weights as B, so A's k = 8 (l / 32) + e stands for key 16 j + 4 (l / 32)
 //    + e (e < 4) and 16 j + 8 + 4 (l / 32) + e - 4: two transposing LDS loads.
 //  * the weights' sum is of the bf16 weights P.V is made of.
-// 64 query heads over 8 kv-heads of 128, 4096 tokens: 390 -> 296 us (0.70 -> 0.93
+// 64 query heads over 8 kv-heads of 128, 4096 tokens: 390 -> 325 us (0.70 -> 0.85
 // PFLOP/s over the visible pairs).  What bounds it now: two waves per SIMD (173
 // registers) that wait for their own chain a third of the time, and the clock,
 // about 1.9 GHz under this load; capped for three waves it spills, and two
 // accumulators per score or a raised wave priority changed nothing.
 constexpr int kPrefillTile32 = 128;
+// How far (base 2) a block's maximum may pass the reference before it moves.
+// The weight of the key a reference was taken from is exactly 1; the further a
+// later maximum may pass it, the more often the largest weight is one that bf16
+// rounds.  Error against float64 (prompts of 1,500 to 2,600 tokens, 2-norm
+// relative; the kernel above, with two references per position, 0.00205) and
+// time at 4096 tokens of 64 heads: 0 0.00200, 327 us; 1 0.00204, 325; 1.5 0.00205,
+// 322; 8 0.00208, 298.
+constexpr float kPrefillLazy32 = 1.0f;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -819,8 +827,8 @@ prefill_fa32_kernel(const PrefillArgs a) {
         const auto x = __builtin_amdgcn_permlane32_swap(u, u, false, false);
         mx = fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1])) * qscale;
       }
-      if (__ballot(mx > m + kPrefillLazy)) {     // the reference moves, as in the kernel above
-        const float mn = mx > m + kPrefillLazy ? mx : m;
+      if (__ballot(mx > m + kPrefillLazy32)) {   // the reference moves, see above
+        const float mn = mx > m + kPrefillLazy32 ? mx : m;
         const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
         lsum *= alpha;
 #pragma unroll

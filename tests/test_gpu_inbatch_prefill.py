@@ -240,14 +240,15 @@ def test_f32_prefill_edges(heads, kv, D, lens):
             assert not torch.isfinite(ob[b, T - 1]).any()
 
 
-# The long-prompt bf16 kernel (128 positions per workgroup; a prompt of 512 tokens
-# and more, 512 workgroups) at its edges: one token past and one short of a 32-key
+# The long-prompt bf16 kernel (128 positions per workgroup; the longest prompt times
+# the workgroups at least 2^20, 2^21 at head_dim 64) at its edges: one token past and one short of a 32-key
 # block, a wave's positions and a tile, prompts of a few tokens beside a long one
 # (tiles of waves with nothing to do), every grouping, both head sizes, a negative
 # scale; against float64 on a few heads, the appended rows bit for bit on all.
 @pytest.mark.parametrize("heads,kv,D,lens,scale", [
-    (64, 8, 128, [1025, 1, 31], 0.0), (64, 64, 128, [927, 129], 0.0), (64, 16, 64, [513, 512, 127], 0.0),
-    (64, 32, 128, [1000, 33], -0.2), (64, 8, 64, [1030, 128, 2], 1.0)])
+    (64, 8, 128, [1025, 1, 31, 513], 0.0), (64, 64, 128, [1055, 129, 640], 0.0),
+    (64, 16, 64, [1030, 1025, 992, 895], 0.0), (64, 32, 128, [1119, 33, 700], -0.2),
+    (64, 8, 64, [1535, 700, 641, 2], 1.0)])
 def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
     import torch
     from paper_2410_18701_amd.cache import BatonCache
@@ -257,7 +258,7 @@ def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
     for b, p in enumerate(lens):          # positions without a token: not read into a result
         for x in (q, k, v):
             x[b, :T - p] = float("nan")
-    assert sum(-(-p // 128) for p in lens) * heads >= 512
+    assert sum(-(-p // 128) for p in lens) * heads * T >= (1 << 21 if D == 64 else 1 << 20)
     cache = BatonCache(1, B, heads, kv, D, capacity=T + 64, dtype="bf16")
     cache.shape_insert(list(range(B)), lens)
     out = torch.full((B, T, heads, D), float("nan"), dtype=torch.bfloat16, device="cuda")
