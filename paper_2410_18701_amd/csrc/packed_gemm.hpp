@@ -535,24 +535,41 @@ __global__ void __launch_bounds__(kRowThreads) reduce_rmsnorm_kernel(
   const int64_t row = blockIdx.x;
   u32x4* yr = reinterpret_cast<u32x4*>(y) + row * vec_per_row;
   float ss = 0.f;
+  u32x4 w0 = {0, 0, 0, 0};   // the thread's first group
   for (int i = threadIdx.x; i < vec_per_row; i += kRowThreads) {
     const int64_t e0 = (row * vec_per_row + i) * 8;   // the group's first element
     const u32x4 old = accumulate ? yr[i] : u32x4{0, 0, 0, 0};
+    float4 v[2];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) v[hf] = *reinterpret_cast<const float4*>(part + e0 + 4 * hf);
+    // the splits in order, four splits' loads in flight (past the last: the last again, not added)
+    for (int32_t s0 = 1; s0 < S; s0 += 4) {
+      float4 q[4][2];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+          q[u][hf] = *reinterpret_cast<const float4*>(part + min(s0 + u, S - 1) * n_out + e0 + 4 * hf);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (s0 + u >= S) break;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          v[hf].x += q[u][hf].x; v[hf].y += q[u][hf].y; v[hf].z += q[u][hf].z; v[hf].w += q[u][hf].w;
+        }
+      }
+    }
     u32x4 w;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
-      float4 v = *reinterpret_cast<const float4*>(part + e0 + 4 * hf);
-      for (int32_t s = 1; s < S; ++s) {
-        const float4 q = *reinterpret_cast<const float4*>(part + s * n_out + e0 + 4 * hf);
-        v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
-      }
       if (accumulate) {
-        v.x += bf16_lo(old[2 * hf]); v.y += bf16_hi(old[2 * hf]);
-        v.z += bf16_lo(old[2 * hf + 1]); v.w += bf16_hi(old[2 * hf + 1]);
+        v[hf].x += bf16_lo(old[2 * hf]); v[hf].y += bf16_hi(old[2 * hf]);
+        v[hf].z += bf16_lo(old[2 * hf + 1]); v[hf].w += bf16_hi(old[2 * hf + 1]);
       }
-      w[2 * hf] = pack_bf16(v.x, v.y);
-      w[2 * hf + 1] = pack_bf16(v.z, v.w);
+      w[2 * hf] = pack_bf16(v[hf].x, v[hf].y);
+      w[2 * hf + 1] = pack_bf16(v[hf].z, v[hf].w);
     }
+    if (i == (int)threadIdx.x) w0 = w;
     yr[i] = w;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -569,7 +586,7 @@ __global__ void __launch_bounds__(kRowThreads) reduce_rmsnorm_kernel(
   for (int w = 0; w < kRowThreads / kWave; ++w) tot += psum[w];
   const float inv = 1.0f / sqrtf(tot * inv_dim + eps);
   for (int i = threadIdx.x; i < vec_per_row; i += kRowThreads) {
-    const u32x4 w = yr[i], gw = g[i];   // this thread's own stores above
+    const u32x4 w = i == (int)threadIdx.x ? w0 : yr[i], gw = g[i];   // this thread's own stores above
     u32x4 o;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
