@@ -16,106 +16,34 @@ namespace {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// How a product runs: the kernel, its tile, and the split along k.
-enum GemmKind { kRowGemm, kSkinnyGemm, kTileGemm };
-struct GemmPlan {
-  GemmKind kind;
-  int32_t mt, ns;       // row tiles of 16 per workgroup, weight slices per wave
-  int32_t chunks;       // row chunks
-  int32_t groups;       // slice groups
-  int32_t tc, splits;   // 32-wide blocks per split, splits along k
-};
-
-// The plan of a product of `rows` rows with `slices` 16-row weight slices
-// (gated: of gate slices, each with its up slice) of kt blocks, `max_splits`
-// the most the workspace holds partial sums for.  The plan depends on the
-// sizes alone, and gated products follow the same rule as ungated ones with
-// one split where their sums must be the same bits: up to 8 rows every product
-// divides k over its workgroup's waves alike, past that unsplit sums run along
-// k in one chain in either kernel.
-GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t kt, bool gated, int32_t max_splits) {
-  GemmPlan p;
-  p.chunks = 1;
-  p.splits = 1;
-  if (rows <= 8) {
-    // A workgroup per slice already divides k over its four waves; with fewer
-    // than 64 slices (a quarter of the CUs) k is split further, at least 64
-    // blocks each.  1 row, us, 1 / 2 / 4 splits: 512 x 8192 9.8 / 8.5 / 7.6,
-    // but 1024 x 4096 6.6 / 7.1 / 7.8 and 2048 x 2048 5.4 / 7.3 / 9.6.
-    p.kind = kRowGemm;
-    p.mt = p.ns = 1;
-    p.groups = slices;
-    if (!gated && slices < 64) p.splits = std::min(4, kt / 64);
-  } else if (rows <= 64 && !gated) {
-    // With fewer than 512 slices (one per wave: two waves per SIMD), split
-    // into about 1024 / slices ranges of at least 8 blocks each: at 64 rows
-    // the split's partial sums and second launch cost more than they gain once
-    // the slices alone give two waves per SIMD.
-    p.kind = kSkinnyGemm;
-    p.mt = (rows + 15) / 16;
-    p.ns = 1;
-    p.groups = (slices + baton::kGemmWaves - 1) / baton::kGemmWaves;
-    if (slices < 512) p.splits = std::min((1024 + slices - 1) / slices, kt / 8);
-  } else {
-    // The tile (slices per wave) and the split that the measured costs favour:
-    // a workgroup's step of 64 along k takes its CU about (2 mt + 8 ns) KB of
-    // loads at 0.022 us a KB, the workgroups run in rounds of 256, and a split
-    // costs a launch (4 us) and writes and reads its partial sums (5 TB/s).
-    // llama2-7b, modelled / measured us: QKV at 256 rows 3 slices, 2 splits
-    // 43 / 42 (2 slices, 1 split 46 / 46), down at 256 rows 2 slices, 4 splits
-    // 41 / 40 (3 and 5: 44 / 45), QKV at 128 rows 2 and 2 31 / 33 (1 and 1
-    // 34 / 34), gate/up at 128 rows 2 slices 45 / 51 (3: 56 / 62, 1: 67 / 61).
-    p.kind = kTileGemm;
-    p.chunks = rows > 128 ? 2 : 1;
-    p.mt = (rows + 16 * p.chunks - 1) / (16 * p.chunks);
-    double best = 0;
-    p.ns = 0;
-    const int32_t n_out = 16 * slices;
-    for (int32_t ns = 1; ns <= (rows > 64 ? 3 : 2); ++ns) {
-      const int32_t per = gated ? 2 * ns : 4 * ns, groups = (slices + per - 1) / per;
-      for (int32_t s = 1; s <= (gated ? 1 : std::min(8, std::max(1, max_splits))); ++s) {
-        const int32_t tc = (kt + s - 1) / s, sn = (kt + tc - 1) / tc;
-        const int64_t rounds = ((int64_t)groups * p.chunks * sn + 255) / 256;
-        const double us = 0.022 * rounds * ((tc + 1) / 2) * (2 * p.mt + 8 * ns) +
-                          (sn > 1 ? 4 + 8e-6 / 5 * sn * rows * (double)n_out : 0);
-        if (p.ns == 0 || us < best) {
-          best = us;
-          p.ns = ns;
-          p.groups = groups;
-          p.splits = sn;
-        }
-      }
-    }
-  }
-  p.splits = std::max(1, std::min(p.splits, max_splits));
-  p.tc = (kt + p.splits - 1) / p.splits;
-  p.splits = (kt + p.tc - 1) / p.tc;
-  return p;
-}
-
+// Launches of one form; false: the form does not exist, nothing is launched.
 template <int MT, int NS, bool GATED>
-void launch_tile_ns(const baton::GemmArgs& a, dim3 grid, hipStream_t s) {
+bool launch_tile_ns(const baton::GemmArgs& a, dim3 grid, hipStream_t s) {
   const dim3 block(baton::kWave * baton::kGemmWaves);
-  if constexpr (MT > 4) {
-    if (a.chunks > 1) {
+  if (a.chunks > 1) {
+    if constexpr (baton::tile_gemm_built(MT, NS, 2, GATED)) {
       hipLaunchKernelGGL((baton::tile_gemm_kernel<MT, NS, 0, GATED>), grid, block, 0, s, a);
-      return;
+      return true;
     }
+  } else if constexpr (baton::tile_gemm_built(MT, NS, 1, GATED)) {
+    hipLaunchKernelGGL((baton::tile_gemm_kernel<MT, NS, 2, GATED>), grid, block, 0, s, a);
+    return true;
   }
-  hipLaunchKernelGGL((baton::tile_gemm_kernel<MT, NS, 2, GATED>), grid, block, 0, s, a);
+  return false;
 }
 
 template <int MT, bool GATED>
-void launch_tile_mt(const baton::GemmArgs& a, int32_t ns, dim3 grid, hipStream_t s) {
-  if constexpr (MT > 4 || GATED) {   // up to 64 rows gated products only
-    if (ns == 1) return launch_tile_ns<MT, 1, GATED>(a, grid, s);
-    if (ns == 2) return launch_tile_ns<MT, 2, GATED>(a, grid, s);
-    if constexpr (MT > 4) launch_tile_ns<MT, 3, GATED>(a, grid, s);
+bool launch_tile_mt(const baton::GemmArgs& a, int32_t ns, dim3 grid, hipStream_t s) {
+  switch (ns) {
+    case 1: return launch_tile_ns<MT, 1, GATED>(a, grid, s);
+    case 2: return launch_tile_ns<MT, 2, GATED>(a, grid, s);
+    case 3: return launch_tile_ns<MT, 3, GATED>(a, grid, s);
+    default: return false;
   }
 }
 
 template <bool GATED>
-void launch_tile(const baton::GemmArgs& a, const GemmPlan& p, dim3 grid, hipStream_t s) {
+bool launch_tile(const baton::GemmArgs& a, const baton::GemmPlan& p, dim3 grid, hipStream_t s) {
   switch (p.mt) {
     case 1: return launch_tile_mt<1, GATED>(a, p.ns, grid, s);
     case 2: return launch_tile_mt<2, GATED>(a, p.ns, grid, s);
@@ -124,38 +52,41 @@ void launch_tile(const baton::GemmArgs& a, const GemmPlan& p, dim3 grid, hipStre
     case 5: return launch_tile_mt<5, GATED>(a, p.ns, grid, s);
     case 6: return launch_tile_mt<6, GATED>(a, p.ns, grid, s);
     case 7: return launch_tile_mt<7, GATED>(a, p.ns, grid, s);
-    default: return launch_tile_mt<8, GATED>(a, p.ns, grid, s);
+    case 8: return launch_tile_mt<8, GATED>(a, p.ns, grid, s);
+    default: return false;
   }
 }
 
 // Launches the product; a.x .. a.K, a.part, a.accumulate and a.gated are set.
-// Returns the number of splits whose partial sums are still to be added.
+// Returns the number of splits whose partial sums are still to be added (1:
+// none), 0 if the plan's form of the kernel does not exist.
 int32_t launch_packed_gemm(baton::GemmArgs& a, int32_t max_splits, hipStream_t s) {
   const bool gated = a.gated > 0;
   a.kt = (a.K + 31) / 32;
-  const GemmPlan p = packed_gemm_plan(a.rows, gated ? a.gated / 16 : (a.N + 15) / 16, a.kt, gated, max_splits);
+  const baton::GemmPlan p =
+      baton::packed_gemm_plan(a.rows, gated ? a.gated / 16 : (a.N + 15) / 16, a.kt, gated, max_splits);
   a.chunks = p.chunks;
   a.groups = p.groups;
   a.tc = p.tc;
   // with several chunks, whole sets of 8 groups (the kernel's XCD-aware dealing)
   const int64_t blocks = p.chunks == 1 ? p.groups : (int64_t)(p.groups + 7) / 8 * 8 * p.chunks;
   const dim3 grid((unsigned)blocks, (unsigned)p.splits), block(baton::kWave * baton::kGemmWaves);
-  if (p.kind == kRowGemm) {
+  bool built = true;
+  if (p.kind == baton::kRowGemm) {
     if (gated) hipLaunchKernelGGL(baton::row_gemm_kernel<true>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(baton::row_gemm_kernel<false>, grid, block, 0, s, a);
-  } else if (p.kind == kSkinnyGemm) {
+  } else if (p.kind == baton::kSkinnyGemm) {
     switch (p.mt) {
       case 1: hipLaunchKernelGGL(baton::skinny_gemm_kernel<1>, grid, block, 0, s, a); break;
       case 2: hipLaunchKernelGGL(baton::skinny_gemm_kernel<2>, grid, block, 0, s, a); break;
       case 3: hipLaunchKernelGGL(baton::skinny_gemm_kernel<3>, grid, block, 0, s, a); break;
-      default: hipLaunchKernelGGL(baton::skinny_gemm_kernel<4>, grid, block, 0, s, a);
+      case 4: hipLaunchKernelGGL(baton::skinny_gemm_kernel<4>, grid, block, 0, s, a); break;
+      default: built = false;
     }
-  } else if (gated) {
-    launch_tile<true>(a, p, grid, s);
   } else {
-    launch_tile<false>(a, p, grid, s);
+    built = gated ? launch_tile<true>(a, p, grid, s) : launch_tile<false>(a, p, grid, s);
   }
-  return p.splits;
+  return built ? p.splits : 0;
 }
 
 }  // namespace
@@ -212,6 +143,7 @@ baton_status linear_packed(int32_t dtype, const void* x, const void* wp, void* y
   const size_t per_split = (size_t)rows * out_dim * sizeof(float);
   const int32_t max_splits = ws && aligned16(ws) ? (int32_t)std::min<size_t>(ws_bytes / per_split, 1024) : 1;
   const int32_t S = launch_packed_gemm(a, max_splits, stream);
+  if (S < 1) return BATON_EINVAL;
   const int64_t n_out = (int64_t)rows * out_dim;
   if (S > 1 && gain) {
     hipLaunchKernelGGL(baton::reduce_rmsnorm_kernel, dim3(rows), dim3(baton::kRowThreads), 0, stream, a.part, a.y, S,
@@ -265,7 +197,7 @@ baton_status baton_linear_packed_silu(int32_t dtype, const void* x, const void* 
   a.K = in_dim;
   a.accumulate = 0;
   a.gated = out_dim / 2;   // never split along k: the epilogue needs the whole sum
-  launch_packed_gemm(a, 1, stream);
+  if (launch_packed_gemm(a, 1, stream) < 1) return BATON_EINVAL;
   return hipGetLastError() == hipSuccess ? BATON_OK : BATON_EHIP;
 }
 

@@ -16,7 +16,7 @@
 // Loads are raw buffer loads whose out-of-range offsets return zeros: x rows
 // past `rows` and k past K need no branch.
 //
-// Three kernels, chosen by the rows (packed_gemm_plan in layer.hip):
+// Three kernels, chosen by the rows (packed_gemm_plan in gemm_plan.hpp):
 //  * up to 8 rows, row_gemm_kernel: no barrier, no LDS until the end;
 //  * 9 to 64 rows, plain products, skinny_gemm_kernel: one slice per wave;
 //  * 9 to 64 rows with the gated activation, and everything past 64 rows,
@@ -26,6 +26,7 @@
 // matrix operations per output), so either gives the same bits.
 #pragma once
 
+#include "gemm_plan.hpp"
 #include "layer_ops.hpp"
 
 namespace baton {
@@ -48,7 +49,6 @@ struct GemmArgs {
   int32_t gated;         // F > 0: w is [gate; up] (2F rows), y [rows][F] = silu(x . gate^T) * (x . up^T)
 };
 
-constexpr int32_t kGemmWaves = 4;            // waves per workgroup
 constexpr uint32_t kGemmOob = 0x80000000u;   // an offset past every buffer's range
 constexpr int32_t kGemmBufWord3 = 0x00020000;
 

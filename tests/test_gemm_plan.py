@@ -1,0 +1,43 @@
+"""The rule that chooses a packed product's kernel, tile and split (host code):
+over the range of sizes every plan covers the product and names a kernel form
+that exists."""
+import random
+
+import pytest
+
+from tests import gemm_plan as G
+
+SIZES = [16, 32, 96, 208, 512, 1024, 1040, 2048, 4096, 5120, 6160, 8192, 10240, 12288, 14336, 16384, 18432, 22016,
+         22048, 24576, 32000, 36864, 65536, 128256]
+INS = [8, 64, 200, 512, 1024, 1536, 2048, 3072, 4096, 4104, 5120, 8192, 11008, 12288, 16384, 28672]
+
+
+@pytest.mark.parametrize("gated", [False, True])
+def test_every_plan_covers_the_product(gated):
+    rng = random.Random(5)
+    for rows in range(1, 257):
+        for out_dim in SIZES + [16 * rng.randint(1, 4096) for _ in range(8)]:
+            out_dim = (out_dim + 31) // 32 * 32 if gated else out_dim
+            for in_dim in INS:
+                for ws in ([0] if gated else [0, 32 << 20]):
+                    what = (rows, out_dim, in_dim, gated, ws)
+                    p = G.plan(rows, out_dim, in_dim, gated, ws)
+                    kt, slices = -(-in_dim // 32), out_dim // 32 if gated else -(-out_dim // 16)
+                    assert p.splits >= 1 and p.splits * p.tc >= kt > (p.splits - 1) * p.tc, what   # no empty split
+                    assert p.splits == 1 or p.splits * rows * out_dim * 4 <= ws, what
+                    per = {G.ROW: 1, G.STAGED: 2 if gated else 4, G.TILE: (2 if gated else 4) * p.ns}[p.kind]
+                    assert p.groups * per >= slices > (p.groups - 1) * per, what
+                    assert p.chunks * p.mt * 16 >= rows > (p.chunks - 1) * p.mt * 16, what
+                    if p.kind == G.TILE:
+                        assert G.tile_built(p.mt, p.ns, p.chunks, gated), what
+                    else:
+                        assert p.ns == 1 and p.chunks == 1 and p.mt <= (1 if p.kind == G.ROW else 4), what
+                        assert rows <= 8 or p.kind == G.STAGED, what
+
+
+def test_forms_that_do_not_exist_are_known():
+    """The launcher asks the same predicate and returns an error for a form that was not built."""
+    for mt, ns, chunks, gated in [(4, 1, 1, False), (1, 1, 1, False), (1, 1, 2, True), (2, 3, 1, True), (9, 1, 2, True),
+                                  (5, 4, 1, False), (0, 1, 1, True), (8, 0, 1, True)]:
+        assert not G.tile_built(mt, ns, chunks, gated), (mt, ns, chunks, gated)
+    assert G.tile_built(8, 3, 2, False) and G.tile_built(4, 2, 1, True) and G.tile_built(5, 1, 1, False)
