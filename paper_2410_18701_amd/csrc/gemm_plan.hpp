@@ -25,26 +25,86 @@ constexpr bool tile_gemm_built(int32_t mt, int32_t ns, int32_t chunks, bool gate
   return mt >= 1 && mt <= 8 && ns >= 1 && (mt > 4 ? ns <= 3 : gated && ns <= 2 && chunks == 1);
 }
 
+// Up to 8 rows: row_gemm_kernel (a workgroup per slice, k over its four waves)
+// or skinny_gemm_kernel (a wave per slice).  Both sides measured over outputs
+// of 192 .. 128,256 and in of 64 .. 20,480 at 1 and 8 rows; us below at 1 row,
+// the row kernel first, outputs x in (gated: rows of [gate; up]).
+inline bool row_kernel(int32_t rows, int32_t slices, int32_t kt, bool gated) {
+  const int32_t groups = gated ? (slices + 1) / 2 : (slices + kGemmWaves - 1) / kGemmWaves;   // of the staged kernel
+  // Short k leaves a wave a fraction of its eight pairs of loads, all of which
+  // it issues: 4096 x 256 4.2 / 3.4, x 512 4.4 / 4.3, x 1024 4.7 / 5.7; 8192 x
+  // 512 6.5 / 4.7, x 1536 8.4 / 8.1, x 2048 9.3 / 9.8; gated 4096 x 512 5.9 /
+  // 5.0, x 1024 6.3 / 6.3, x 2048 7.3 / 9.3, 8192 x 1024 7.3 / 7.0, x 1536
+  // 8.4 / 8.7.
+  if (groups <= 64) return kt >= (gated ? 32 : 16);
+  if (groups <= 128) return kt >= (gated ? 40 : 50);
+  // Few rows, plain, slices an odd multiple of 128 KB apart, which the staged
+  // kernel reads 8% slower than its neighbours and this one, in whole rounds of
+  // its loads, does not: 12288 x 4096 19.1 / 20.7, x 4064 20.9 / 19.9, x 4160
+  // 21.8 / 19.4, x 8192 35.3 / 33.6, x 12288 48.5 / 51.4, 32000 x 4096 0.92 of
+  // the time; but gated 12288 x 4096 21.8 / 19.5, and at 8 rows 20.2 / 20.5.
+  if (!gated && rows <= 4 && kt % 256 == 128) return true;
+  // One round of the staged kernel on more than half of the CUs: 10240 x 2048
+  // 12.0 / 10.3, x 8192 32.2 / 29.7, 16384 x 512 11.0 / 5.7, x 11008 58.8 /
+  // 56.0; gated 10240 x 4096 20.8 / 17.7.
+  if (groups <= 256) return false;
+  // Several rounds, the last of them poorly filled: 18432 x 2048 18.3 / 20.2, x
+  // 4096 28.7 / 38.0, 22016 x 4096 33.1 / 38.2, x 8192 60.7 / 68.7, gated 58.9 /
+  // 68.3; 36864 x 4096 0.82 of the time, 40960 0.86.  Well filled: 32768 x 2048
+  // 1.13 times, x 8192 1.00, 65536 x 5120 1.10.  Short k: 18432 x 1536 16.7 /
+  // 15.9, 22016 x 1024 17.2 / 11.9, x 2048 20.7 / 20.4.
+  const int64_t room = (int64_t)(groups + 255) / 256 * 256;
+  return 2 * room >= 3 * (int64_t)groups ? kt >= 64 : 5 * room >= 6 * (int64_t)groups && kt >= 128;
+}
+
+// Splits along k of row_gemm_kernel with a few slices.  A wave runs its quarter
+// of the range in rounds of 16 blocks, about 1.6 us each; a second launch and
+// the partial sums cost about 1.5, with many slices more.  So up to one round
+// per wave and one workgroup per CU, the fewest ranges that give that many
+// rounds, and only where that saves enough of them.  1 row, us, 1 / 2 / 3 / 4 /
+// 8 splits: 512 x 4096 5.8 / 5.9 / 6.0 / 6.3 / 7.0, x 6144 7.7 / 7.6 / 6.1 / 6.5
+// / 7.2, x 16384 15.3 / 11.0 / 9.9 / 8.7 / 8.7; 1024 x 16384 16.2 / 12.3 / 11.2
+// / 11.5 / 13.4; 2048 x 8192 10.6 / 10.6, x 11008 14.0 / 12.3 / 14.5; 192 x 4096
+// 5.8 / 5.8, at 8 rows 6.8 / 6.4.
+inline int32_t row_splits(int32_t slices, int32_t kt, int32_t max_splits) {
+  auto rounds = [&](int32_t s) {
+    const int32_t pairs = ((kt + s - 1) / s + 1) / 2;
+    return ((pairs + kGemmWaves - 1) / kGemmWaves + 7) / 8;
+  };
+  const int32_t most = std::min({(kt + 63) / 64, 256 / slices, 8, max_splits});
+  if (most < 2 || rounds(1) - rounds(most) < (slices <= 24 ? 1 : slices < 128 ? 2 : 3)) return 1;
+  int32_t s = 1;
+  while (rounds(s) > rounds(most)) ++s;
+  return s;
+}
+
 // The plan of a product of `rows` rows with `slices` 16-row weight slices
 // (gated: of gate slices, each with its up slice) of kt blocks, `max_splits`
 // the most the workspace holds partial sums for.  The plan depends on the
-// sizes alone, and gated products follow the same rule as ungated ones with
-// one split where their sums must be the same bits: up to 8 rows every product
-// divides k over its workgroup's waves alike, past that unsplit sums run along
-// k in one chain in either kernel.
+// sizes alone.  Any kernel it may take for a row count sums an unsplit product
+// in the same order, gated or not, so the choice never changes its bits.
 inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t kt, bool gated, int32_t max_splits) {
   GemmPlan p;
   p.chunks = 1;
   p.splits = 1;
   if (rows <= 8) {
-    // A workgroup per slice already divides k over its four waves; with fewer
-    // than 64 slices (a quarter of the CUs) k is split further, at least 64
-    // blocks each.  1 row, us, 1 / 2 / 4 splits: 512 x 8192 9.8 / 8.5 / 7.6,
-    // but 1024 x 4096 6.6 / 7.1 / 7.8 and 2048 x 2048 5.4 / 7.3 / 9.6.
-    p.kind = kRowGemm;
     p.mt = p.ns = 1;
-    p.groups = slices;
-    if (!gated && slices < 64) p.splits = std::min(4, kt / 64);
+    p.kind = row_kernel(rows, slices, kt, gated) ? kRowGemm : kSkinnyGemm;
+    if (p.kind == kRowGemm && !gated && max_splits > 1) {
+      if (slices > 256 && slices <= 384 && kt >= 96 && (kt >= 160 || kt % 64)) {
+        // Up to 1.5 workgroups per CU of the kernel with a slice per
+        // workgroup: the second round is half empty.  The staged kernel in two
+        // ranges of k, 1 row, us, row kernel / this: 5120 x 3072 11.1 / 10.8,
+        // 6144 x 5120 16.2 / 15.4, 6144 x 16384 41.9 / 35.5; but 6144 x 4096
+        // (whole rounds of the row kernel's loads) 12.5 / 14.7, and 7168 x 8192
+        // 23.0 / 24.9.
+        p.kind = kSkinnyGemm;
+        p.splits = 2;
+      } else if (slices <= 128) {
+        p.splits = row_splits(slices, kt, max_splits);
+      }
+    }
+    p.groups = p.kind == kRowGemm ? slices : gated ? (slices + 1) / 2 : (slices + kGemmWaves - 1) / kGemmWaves;
   } else if (rows <= 64 && !gated) {
     // With fewer than 512 slices (one per wave: two waves per SIMD), split
     // into about 1024 / slices ranges of at least 8 blocks each: at 64 rows

@@ -57,6 +57,24 @@ bool launch_tile(const baton::GemmArgs& a, const baton::GemmPlan& p, dim3 grid, 
   }
 }
 
+template <bool GATED>
+bool launch_skinny(const baton::GemmArgs& a, const baton::GemmPlan& p, dim3 grid, hipStream_t s) {
+  const dim3 block(baton::kWave * baton::kGemmWaves);
+  if (a.rows <= 8) {
+    hipLaunchKernelGGL((baton::skinny_gemm_kernel<1, GATED, true>), grid, block, 0, s, a);
+    return true;
+  }
+  if constexpr (!GATED) {
+    switch (p.mt) {
+      case 1: hipLaunchKernelGGL((baton::skinny_gemm_kernel<1, GATED, false>), grid, block, 0, s, a); return true;
+      case 2: hipLaunchKernelGGL((baton::skinny_gemm_kernel<2, GATED, false>), grid, block, 0, s, a); return true;
+      case 3: hipLaunchKernelGGL((baton::skinny_gemm_kernel<3, GATED, false>), grid, block, 0, s, a); return true;
+      case 4: hipLaunchKernelGGL((baton::skinny_gemm_kernel<4, GATED, false>), grid, block, 0, s, a); return true;
+    }
+  }
+  return false;
+}
+
 // Launches the product; a.x .. a.K, a.part, a.accumulate and a.gated are set.
 // Returns the number of splits whose partial sums are still to be added (1:
 // none), 0 if the plan's form of the kernel does not exist.
@@ -76,13 +94,7 @@ int32_t launch_packed_gemm(baton::GemmArgs& a, int32_t max_splits, hipStream_t s
     if (gated) hipLaunchKernelGGL(baton::row_gemm_kernel<true>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(baton::row_gemm_kernel<false>, grid, block, 0, s, a);
   } else if (p.kind == baton::kSkinnyGemm) {
-    switch (p.mt) {
-      case 1: hipLaunchKernelGGL(baton::skinny_gemm_kernel<1>, grid, block, 0, s, a); break;
-      case 2: hipLaunchKernelGGL(baton::skinny_gemm_kernel<2>, grid, block, 0, s, a); break;
-      case 3: hipLaunchKernelGGL(baton::skinny_gemm_kernel<3>, grid, block, 0, s, a); break;
-      case 4: hipLaunchKernelGGL(baton::skinny_gemm_kernel<4>, grid, block, 0, s, a); break;
-      default: built = false;
-    }
+    built = gated ? launch_skinny<true>(a, p, grid, s) : launch_skinny<false>(a, p, grid, s);
   } else {
     built = gated ? launch_tile<true>(a, p, grid, s) : launch_tile<false>(a, p, grid, s);
   }

@@ -17,13 +17,16 @@
 // past `rows` and k past K need no branch.
 //
 // Three kernels, chosen by the rows (packed_gemm_plan in gemm_plan.hpp):
-//  * up to 8 rows, row_gemm_kernel: no barrier, no LDS until the end;
+//  * up to 8 rows, row_gemm_kernel: no barrier, no LDS until the end; where it
+//    is not the faster one, skinny_gemm_kernel;
 //  * 9 to 64 rows, plain products, skinny_gemm_kernel: one slice per wave;
 //  * 9 to 64 rows with the gated activation, and everything past 64 rows,
 //    tile_gemm_kernel: one to three slices per wave, the LDS reads of the
 //    activations pipelined ahead of the matrix operations.
-// Unsplit, the last two add along k in the same order (one chain of 32-wide
-// matrix operations per output), so either gives the same bits.
+// Unsplit, the kernels that a row count may take add along k in the same order
+// -- up to 8 rows the sums of four ranges of k, past that one chain of 32-wide
+// matrix operations per output -- so either gives the same bits, and a gated
+// product those of the plain one and the activation.
 #pragma once
 
 #include "gemm_plan.hpp"
@@ -84,6 +87,11 @@ __global__ void __launch_bounds__(256) pack_weight_kernel(const u32x4* __restric
   wp[i] = (n < N && k < K) ? w[((int64_t)n * K + k) / 8] : u32x4{0, 0, 0, 0};
 }
 
+// Up to 8 rows the sum over `blocks` 32-wide blocks is of four ranges of k added
+// in order; this is a range's length in batches of four blocks (the last ranges
+// may be shorter or empty).
+__device__ __forceinline__ int32_t four_ranges(int32_t blocks) { return ((blocks + 3) / 4 + 3) / 4; }
+
 // The four outputs (m, n .. n + 3) of a lane: the split's partial sum, or y.
 __device__ __forceinline__ void gemm_store(const GemmArgs& a, int32_t m, int32_t n, gemm_f32x4 v) {
   if (gridDim.y > 1) {
@@ -100,6 +108,30 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& a, int32_t m, int32_t
 
 __device__ __forceinline__ uint2 pack_bf16x4(const gemm_f32x4& v) {
   return make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+}
+
+// The gated epilogue of a workgroup whose waves w and w + 2 (w < 2) hold a gate
+// slice set and the up slices of the same columns, the same (row, column) places
+// in each: every wave finishes every other tile, the gate wave the even ones, the
+// up wave the odd ones, the other's outputs (rounded to bf16) reaching it through
+// lds.  gs0 is the pair's first gate slice; rows row0 .. row0 + rows - 1 are written.
+template <int NS, int MT>
+__device__ __forceinline__ void gemm_gated_store(const GemmArgs& a, uint8_t* lds, const gemm_f32x4 (&acc)[NS][MT], int w,
+                                                 int lane, int32_t gs0, int32_t row0, int32_t rows) {
+  uint2* ex = reinterpret_cast<uint2*>(lds) + (w % 2) * NS * MT * kWave + lane;
+  const int up = w / 2, c16 = lane % 16, g4 = lane / 16;
+#pragma unroll
+  for (int q = 0; q < NS * MT; ++q)
+    if (q % 2 != up) ex[q * kWave] = pack_bf16x4(acc[q / MT][q % MT]);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NS * MT; ++q) {
+    if (q % 2 != up) continue;
+    const int32_t n = 16 * (gs0 + q / MT) + 4 * g4, m = 16 * (q % MT) + c16;
+    if (n >= a.gated || m >= rows) continue;
+    const uint2 own = pack_bf16x4(acc[q / MT][q % MT]), other = ex[q * kWave];
+    *reinterpret_cast<uint2*>(a.y + (int64_t)(row0 + m) * a.gated + n) = up ? silu_mul4(other, own) : silu_mul4(own, other);
+  }
 }
 
 // ---------------------------------------------------------- up to 8 rows --
@@ -129,8 +161,8 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) row_gemm_kernel(const Gemm
   const int lane = threadIdx.x % kWave, c16 = lane % 16, g4 = lane / 16;
   const int32_t grp = blockIdx.x;
   const int32_t t_begin = blockIdx.y * a.tc, t_end = min(a.kt, t_begin + a.tc);
-  // this wave's pairs of blocks
-  const int32_t np = (t_end - t_begin + 1) / 2, per = (np + kGemmWaves - 1) / kGemmWaves;
+  // this wave's pairs of blocks, an even number of them (whole batches of the staged kernel)
+  const int32_t np = (t_end - t_begin + 1) / 2, per = 2 * four_ranges(t_end - t_begin);
   const int32_t p0 = min(w * per, np), p1 = min(p0 + per, np);
   const uint32_t row_bytes = (uint32_t)a.K * 2u;
   __amdgpu_buffer_rsrc_t rw[NS];
@@ -186,8 +218,9 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) row_gemm_kernel(const Gemm
     gemm_store(a, c16, n, acc[0]);
 }
 
-// ------------------------------------------------- 9 to 64 rows, ungated --
-// A wave owns one slice (four per workgroup), the workgroup all the rows.  The
+// ------------ 9 to 64 rows, ungated, and up to 8 rows where it is faster --
+// A wave owns one slice (four per workgroup; gated: two gate slices and their
+// up slices), the workgroup all the rows.  The
 // activation rows are staged in LDS per batch of four blocks, each row padded
 // by 16 bytes so that the 16 rows one B-operand read spans fall in different
 // banks; when there are too few slices to occupy the GPU the blocks are also
@@ -195,7 +228,7 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) row_gemm_kernel(const Gemm
 // tile_gemm_kernel with one slice per wave is no faster here (llama2-7b at 64
 // rows: QKV 25.6 against 25.4 us, output 14.1 against 14.8, down 23.7 against
 // 23.8; at 16 rows QKV 22.5 against 21.4, down 20.4 against 19.4).
-template <int MG>
+template <int MG, bool GATED, bool FOUR>
 __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const GemmArgs a) {
   constexpr int KU = 4, P = 4;                     // blocks per batch; register sets of the load pipeline
   constexpr int kRows = 64;                        // staged rows (past `rows`: zeros)
@@ -206,18 +239,22 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const G
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int lane = tid % kWave, c16 = lane % 16, g4 = lane / 16;
-  const int32_t slice = (int32_t)blockIdx.x * kGemmWaves + w;
+  // Gated: waves 0 and 1 take two gate slices, waves 2 and 3 their up slices.
+  static_assert(kGemmWaves == 4, "the gated epilogue pairs two gate and two up waves");
+  const int32_t gate = 2 * (int32_t)blockIdx.x + w % 2;
+  const int32_t slice = GATED ? gate + (w < 2 ? 0 : a.gated / 16) : (int32_t)blockIdx.x * kGemmWaves + w;
+  const int32_t s_end = GATED && w < 2 ? a.gated / 16 : (a.N + 15) / 16;   // this wave's slices end here
   const int32_t t_begin = blockIdx.y * a.tc, t_end = min(a.kt, t_begin + a.tc);
   const uint32_t row_bytes = (uint32_t)a.K * 2u;
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(   // empty past N (loads zeros, writes nothing)
-      const_cast<uint16_t*>(a.wp) + ((int64_t)min(slice, (a.N + 15) / 16) * a.kt + t_begin) * 512, 0,
-      16 * slice < a.N ? (t_end - t_begin) * 1024 : 0, kGemmBufWord3);
+      const_cast<uint16_t*>(a.wp) + ((int64_t)min(slice, s_end - 1) * a.kt + t_begin) * 512, 0,
+      slice < s_end ? (t_end - t_begin) * 1024 : 0, kGemmBufWord3);
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(a.x), 0, (int32_t)(a.rows * row_bytes), kGemmBufWord3);
 
-  gemm_f32x4 acc[MG];
+  gemm_f32x4 acc[1][MG];
 #pragma unroll
-  for (int j = 0; j < MG; ++j) acc[j] = gemm_f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < MG; ++j) acc[0][j] = gemm_f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Loads of batch b (blocks t_begin + KU b ...): the workgroup's activation
   // pieces (thread tid: pieces tid + 256 i -- row p / (4 KU), 16 bytes at
@@ -244,7 +281,22 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const G
       *reinterpret_cast<u32x4*>(&xs[buf][(p / kPieces) * kRow + (p % kPieces) * 16]) = xr[i];
     }
   };
-  auto mult = [&](int buf, const u32x4 (&wr)[KU]) {
+  // FOUR: the sum of each of the four ranges of k that row_gemm_kernel's waves
+  // take by itself, the ranges added in the waves' order (the same bits).
+  const int32_t range = four_ranges(t_end - t_begin);   // batches
+  int32_t next = range, passed = 0;
+  gemm_f32x4 tot[MG];
+  auto mult = [&](int32_t b, const u32x4 (&wr)[KU]) {
+    if (FOUR && b == next) {   // the same for the whole workgroup
+#pragma unroll
+      for (int j = 0; j < MG; ++j) {
+        tot[j] = passed ? tot[j] + acc[0][j] : acc[0][j];
+        acc[0][j] = gemm_f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      next += range;
+      ++passed;
+    }
+    const int buf = b & 1;
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
       u32x4 xb[MG];
@@ -252,7 +304,7 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const G
       for (int j = 0; j < MG; ++j)
         xb[j] = *reinterpret_cast<const u32x4*>(&xs[buf][(16 * j + c16) * kRow + (32 * u + 8 * g4) * 2]);
 #pragma unroll
-      for (int j = 0; j < MG; ++j) acc[j] = gemm_mfma(wr[u], xb[j], acc[j]);
+      for (int j = 0; j < MG; ++j) acc[0][j] = gemm_mfma(wr[u], xb[j], acc[0][j]);
     }
   };
   // P register sets: while batch b is multiplied, batches b + 1 .. b + P - 1
@@ -272,7 +324,7 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const G
 #define BATON_GEMM_STEP(S)                                               \
   issue(b + (S) + P - 1, xr[((S) + P - 1) % P], wr[((S) + P - 1) % P]); \
   __builtin_amdgcn_sched_barrier(0);                                     \
-  mult((b + (S)) & 1, wr[(S) % P]);                                      \
+  mult(b + (S), wr[(S) % P]);                                            \
   stage((b + (S) + 1) & 1, xr[((S) + 1) % P]);                           \
   __syncthreads();
     // A counted loop with no exit inside its body (an exit between the steps
@@ -292,12 +344,23 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const G
     }
 #undef BATON_GEMM_STEP
   }
+  if constexpr (FOUR) {
+#pragma unroll
+    for (int j = 0; j < MG; ++j) {
+      if (passed) acc[0][j] = tot[j] + acc[0][j];
+      if (passed < 3) acc[0][j] += gemm_f32x4{0.f, 0.f, 0.f, 0.f};   // the empty ranges
+    }
+  }
+  if constexpr (GATED) {
+    gemm_gated_store<1, MG>(a, &xs[0][0], acc, w, lane, gate, 0, a.rows);
+    return;
+  }
   const int32_t n = 16 * slice + 4 * g4;
   if (n >= a.N) return;
 #pragma unroll
   for (int j = 0; j < MG; ++j) {
     const int32_t m = 16 * j + c16;
-    if (m < a.rows) gemm_store(a, m, n, acc[j]);
+    if (m < a.rows) gemm_store(a, m, n, acc[0][j]);
   }
 }
 
@@ -469,25 +532,7 @@ __global__ void __launch_bounds__(256) tile_gemm_kernel(const GemmArgs a) {
   if (b + 1 < n_batch) BATON_TILE_STEP(b + 1, 1)
 #undef BATON_TILE_STEP
   if constexpr (GATED) {
-    // Gate wave w and up wave w + 2 hold the same (row, column) places; each
-    // finishes every other tile of them: the gate wave the even ones, the up
-    // wave the odd ones.
-    uint2* ex = reinterpret_cast<uint2*>(lds) + (w % 2) * NS * MT * kWave + lane;
-    auto packed = [&](int q) { return pack_bf16x4(acc[q / MT][q % MT]); };
-    const int up = w / 2;
-#pragma unroll
-    for (int q = 0; q < NS * MT; ++q)
-      if (q % 2 != up) ex[q * kWave] = packed(q);
-    __syncthreads();
-    const int32_t gs0 = 2 * NS * grp + NS * (w % 2);   // the pair's first gate slice
-#pragma unroll
-    for (int q = 0; q < NS * MT; ++q) {
-      if (q % 2 != up) continue;
-      const int32_t n = 16 * (gs0 + q / MT) + 4 * g4, m = 16 * (q % MT) + c16;
-      if (n >= a.gated || m >= rows) continue;
-      const uint2 own = packed(q), other = ex[q * kWave];
-      *reinterpret_cast<uint2*>(a.y + (int64_t)(row0 + m) * a.gated + n) = up ? silu_mul4(other, own) : silu_mul4(own, other);
-    }
+    gemm_gated_store<NS, MT>(a, lds, acc, w, lane, 2 * NS * grp + NS * (w % 2), row0, rows);
     return;
   }
 #pragma unroll

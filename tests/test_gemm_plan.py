@@ -32,7 +32,7 @@ def test_every_plan_covers_the_product(gated):
                         assert G.tile_built(p.mt, p.ns, p.chunks, gated), what
                     else:
                         assert p.ns == 1 and p.chunks == 1 and p.mt <= (1 if p.kind == G.ROW else 4), what
-                        assert rows <= 8 or p.kind == G.STAGED, what
+                        assert rows <= 8 or (p.kind == G.STAGED and not gated), what
 
 
 def test_forms_that_do_not_exist_are_known():
@@ -41,3 +41,17 @@ def test_forms_that_do_not_exist_are_known():
                                   (5, 4, 1, False), (0, 1, 1, True), (8, 0, 1, True)]:
         assert not G.tile_built(mt, ns, chunks, gated), (mt, ns, chunks, gated)
     assert G.tile_built(8, 3, 2, False) and G.tile_built(4, 2, 1, True) and G.tile_built(5, 1, 1, False)
+
+
+# (rows, out, in, gated, kind, least workgroups): sizes at which the wrong kernel or
+# too few workgroups measured 1.1 to 1.9 times the time of the right one, up to 8 rows.
+@pytest.mark.parametrize("rows,out_dim,in_dim,gated,kind,least", [
+    (1, 8192, 512, False, G.STAGED, 128), (8, 16384, 512, False, G.STAGED, 256), (1, 16384, 2048, False, G.STAGED, 256),
+    (1, 32768, 512, True, G.STAGED, 512), (8, 1024, 512, True, G.STAGED, 16), (4, 16384, 1024, True, G.STAGED, 256),
+    (8, 10240, 16384, True, G.STAGED, 160), (1, 10240, 2048, False, G.STAGED, 160),
+    (1, 22016, 4096, True, G.ROW, 688), (8, 18432, 8192, False, G.ROW, 1152), (1, 4096, 4096, False, G.ROW, 256),
+    (1, 512, 16384, False, G.ROW, 256), (8, 1024, 16384, False, G.ROW, 256), (1, 192, 16384, False, G.ROW, 96),
+    (1, 2048, 11008, False, G.ROW, 256), (1, 512, 4096, False, G.ROW, 32), (8, 6144, 16384, False, G.STAGED, 192)])
+def test_up_to_8_rows(rows, out_dim, in_dim, gated, kind, least):
+    p = G.plan(rows, out_dim, in_dim, gated)
+    assert p.kind == kind and p.groups * p.splits >= least, p

@@ -20,6 +20,7 @@ import oracle.baton_oracle as O
 import oracle.llama_layer as LL
 from paper_2410_18701_amd import layer as PL
 from paper_2410_18701_amd.cache import BatonCache
+from tests import gemm_plan as G
 from tests import parity
 from workload import driver, gen
 from workload import model as M
@@ -208,6 +209,50 @@ def test_packed_products_edges(rows, in_dim, out_dim, ws):
     _close(_val(ap[:rows].contiguous()), LL.silu(want[:, :F]) * want[:, F:], rel=2.0 ** -6, atol=4e-3, what="gated")
     for t in (yp, y2, ap):
         assert torch.isnan(t[rows:]).all(), "written past the last row"
+    g.close()
+
+
+# Up to 8 rows either of two kernels, by the sizes: the choice for a gated product
+# and for the plain one of the same weight need not be the same, the bits are
+# (12288 x 4096 at 1 row and 2048 x 600 take one each).  The products that split
+# along k: ranges of the kernel with a workgroup per slice (few outputs, long k),
+# and two ranges of the staged one (5200 x 3080).
+@pytest.mark.parametrize("rows,F,in_dim,kinds", [
+    (1, 6144, 4096, (G.ROW, G.STAGED)), (3, 1024, 600, (G.ROW, G.STAGED)), (8, 5120, 520, (G.STAGED, G.STAGED)),
+    (7, 48, 200, (G.STAGED, G.STAGED)), (8, 8176, 2056, (G.STAGED, G.STAGED)), (2, 16384, 72, (G.STAGED, G.STAGED)),
+    (8, 11008, 1032, (G.STAGED, G.STAGED)), (5, 1040, 1096, (G.ROW, G.ROW))])
+def test_kernels_of_up_to_8_rows_agree(rows, F, in_dim, kinds):
+    assert (G.plan(rows, 2 * F, in_dim, False, 0).kind, G.plan(rows, 2 * F, in_dim, True).kind) == kinds
+    rng = np.random.default_rng(rows + F + in_dim)
+    xb, wb = _bits(rng, (rows, in_dim)), _bits(rng, (2 * F, in_dim), round(np.log2(in_dim) / 2))
+    g = PL.Gemm(ws_bytes=0)
+    x, wp = _dev(xb), g.pack(_dev(wb))
+    gu, out = (torch.full((rows, n), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (2 * F, F))
+    ref = torch.empty_like(out)
+    g.linear_packed(x, wp, gu)
+    PL.silu_mul(gu, ref)
+    g.linear_packed_silu(x, wp, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(parity.host_bits(out), parity.host_bits(ref)), "fused against linear_packed + silu_mul"
+    _close(_val(gu), LL.linear(O.widen(xb, O.BF16), O.widen(wb, O.BF16)), what="gate_up")
+    g.close()
+
+
+@pytest.mark.parametrize("rows,out_dim,in_dim,kind,splits", [
+    (8, 192, 16384, G.ROW, 8), (1, 2048, 11008, G.ROW, 2), (5, 1024, 5128, G.ROW, 3), (3, 5200, 3080, G.STAGED, 2)])
+def test_split_products_of_up_to_8_rows(rows, out_dim, in_dim, kind, splits):
+    p = G.plan(rows, out_dim, in_dim)
+    assert (p.kind, p.splits) == (kind, splits)
+    rng = np.random.default_rng(rows + out_dim + in_dim)
+    xb, yb = _bits(rng, (rows, in_dim)), _bits(rng, (rows, out_dim))
+    wb = _bits(rng, (out_dim, in_dim), round(np.log2(in_dim) / 2))
+    g = PL.Gemm()
+    x, wp, y, y2 = _dev(xb), g.pack(_dev(wb)), torch.empty((rows, out_dim), dtype=torch.bfloat16, device="cuda"), _dev(yb)
+    g.linear_packed(x, wp, y)
+    g.linear_packed(x, wp, y2, accumulate=True)
+    want = LL.linear(O.widen(xb, O.BF16), O.widen(wb, O.BF16))
+    _close(_val(y), want, what="linear_packed")
+    _close(_val(y2), O.widen(yb, O.BF16) + want, what="accumulate")
     g.close()
 
 
