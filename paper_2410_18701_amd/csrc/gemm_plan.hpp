@@ -30,6 +30,8 @@ constexpr bool tile_gemm_built(int32_t mt, int32_t ns, int32_t chunks, bool gate
 // of 192 .. 128,256 and in of 64 .. 20,480 at 1 and 8 rows; us below at 1 row,
 // the row kernel first, outputs x in (gated: rows of [gate; up]).
 inline bool row_kernel(int32_t rows, int32_t slices, int32_t kt, bool gated) {
+  // Its launch has a workgroup, 256 threads, per slice, of less than 2^32 in all.
+  if (slices >= 1 << 24) return false;
   const int32_t groups = gated ? (slices + 1) / 2 : (slices + kGemmWaves - 1) / kGemmWaves;   // of the staged kernel
   // Short k leaves a wave a fraction of its eight pairs of loads, all of which
   // it issues: 4096 x 256 4.2 / 3.4, x 512 4.4 / 4.3, x 1024 4.7 / 5.7; 8192 x

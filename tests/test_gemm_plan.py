@@ -55,3 +55,13 @@ def test_forms_that_do_not_exist_are_known():
 def test_up_to_8_rows(rows, out_dim, in_dim, gated, kind, least):
     p = G.plan(rows, out_dim, in_dim, gated)
     assert p.kind == kind and p.groups * p.splits >= least, p
+
+
+def test_launches_stay_below_2_to_the_32_threads():
+    """Weights of 2^28 outputs and more, which a workgroup per slice cannot launch."""
+    for rows in (1, 8, 9, 64, 65, 256):
+        for out_dim in ((1 << 28) - 16, 1 << 28, 1 << 29):
+            for in_dim in (32, 96, 2048, 4096):
+                for gated in (False, True):
+                    p = G.plan(rows, out_dim, in_dim, gated)
+                    assert p.groups * p.chunks * p.splits * 256 < 1 << 32, (rows, out_dim, in_dim, gated, p)
