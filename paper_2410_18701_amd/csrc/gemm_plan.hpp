@@ -38,7 +38,7 @@ inline bool row_kernel(int32_t rows, int32_t slices, int32_t kt, bool gated) {
   // 512 6.5 / 4.7, x 1536 8.4 / 8.1, x 2048 9.3 / 9.8; gated 4096 x 512 5.9 /
   // 5.0, x 1024 6.3 / 6.3, x 2048 7.3 / 9.3, 8192 x 1024 7.3 / 7.0, x 1536
   // 8.4 / 8.7.
-  if (groups <= 64) return kt >= (gated ? 32 : 16);
+  if (groups <= 64) return kt >= (gated ? 30 : 16);
   if (groups <= 128) return kt >= (gated ? 40 : 50);
   // Few rows, plain, slices an odd multiple of 128 KB apart, which the staged
   // kernel reads 8% slower than its neighbours and this one, in whole rounds of
@@ -117,6 +117,32 @@ inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t kt, bool 
     p.ns = 1;
     p.groups = (slices + kGemmWaves - 1) / kGemmWaves;
     if (slices < 512) p.splits = std::min((1024 + slices - 1) / slices, kt / 8);
+  } else if (rows <= 64) {
+    // Gated.  As long as the staged kernel's workgroups make one round, its four
+    // blocks per barrier against the tile's two, one slice per wave in both: 16
+    // rows, us, staged / tile, gate and up rows x in: 1024 x 8192 26.5 / 32.1,
+    // 8192 x 4096 17.2 / 20.0, x 896 7.0 / 7.4 (14144), x 512 5.1 / 5.0, 16384 x 4096
+    // 24.6 / 24.8; 64 rows, whose activations the tile reads ahead, 4096 x 8192
+    // 40.2 / 42.1, x 2048 13.4 / 13.2, x 1024 8.9 / 8.7.
+    p.groups = (slices + 1) / 2;
+    p.mt = (rows + 15) / 16;
+    p.ns = 1;
+    if (p.groups <= 256 && kt >= (rows <= 48 ? 24 : 128)) {
+      p.kind = kSkinnyGemm;
+    } else {
+      // Two slices per wave where that makes one round of two and a workgroup
+      // has enough work: one / two, us, 22016 x 4096 at 9 rows 32.8 / 34.1, 32
+      // 37.2 / 36.1, 64 44.9 / 40.9, x 8192 at 16 65.2 / 63.3, at 32 70.9 / 66.2;
+      // 26304 x 3216 at 48 40.7 / 35.3; two over one at 64 rows of 512 in 1.00 to
+      // 1.10, of 1024 0.95 to 0.99; 30720 x 4096 at 64 1.01, x 8192 0.89; more
+      // rounds, 36864 and up, 1.02 to 1.24 at any k.
+      p.kind = kTileGemm;
+      if (p.groups > 256 && p.groups <= 512 &&
+          (rows > 32 ? kt >= (p.groups <= 430 ? 24 : 200) : rows > 16 && kt >= 200)) {
+        p.ns = 2;
+        p.groups = (slices + 3) / 4;
+      }
+    }
   } else {
     // The tile (slices per wave) and the split that the measured costs favour:
     // a workgroup's step of 64 along k takes its CU about (2 mt + 8 ns) KB of
@@ -132,7 +158,7 @@ inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t kt, bool 
     double best = 0;
     p.ns = 0;
     const int32_t n_out = 16 * slices;
-    for (int32_t ns = 1; ns <= (rows > 64 ? 3 : 2); ++ns) {
+    for (int32_t ns = 1; ns <= 3; ++ns) {
       const int32_t per = gated ? 2 * ns : 4 * ns, groups = (slices + per - 1) / per;
       for (int32_t s = 1; s <= (gated ? 1 : std::min(8, std::max(1, max_splits))); ++s) {
         const int32_t tc = (kt + s - 1) / s, sn = (kt + tc - 1) / tc;

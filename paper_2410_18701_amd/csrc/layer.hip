@@ -64,15 +64,13 @@ bool launch_skinny(const baton::GemmArgs& a, const baton::GemmPlan& p, dim3 grid
     hipLaunchKernelGGL((baton::skinny_gemm_kernel<1, GATED, true>), grid, block, 0, s, a);
     return true;
   }
-  if constexpr (!GATED) {
-    switch (p.mt) {
-      case 1: hipLaunchKernelGGL((baton::skinny_gemm_kernel<1, GATED, false>), grid, block, 0, s, a); return true;
-      case 2: hipLaunchKernelGGL((baton::skinny_gemm_kernel<2, GATED, false>), grid, block, 0, s, a); return true;
-      case 3: hipLaunchKernelGGL((baton::skinny_gemm_kernel<3, GATED, false>), grid, block, 0, s, a); return true;
-      case 4: hipLaunchKernelGGL((baton::skinny_gemm_kernel<4, GATED, false>), grid, block, 0, s, a); return true;
-    }
+  switch (p.mt) {
+    case 1: hipLaunchKernelGGL((baton::skinny_gemm_kernel<1, GATED, false>), grid, block, 0, s, a); return true;
+    case 2: hipLaunchKernelGGL((baton::skinny_gemm_kernel<2, GATED, false>), grid, block, 0, s, a); return true;
+    case 3: hipLaunchKernelGGL((baton::skinny_gemm_kernel<3, GATED, false>), grid, block, 0, s, a); return true;
+    case 4: hipLaunchKernelGGL((baton::skinny_gemm_kernel<4, GATED, false>), grid, block, 0, s, a); return true;
+    default: return false;
   }
-  return false;
 }
 
 // Launches the product; a.x .. a.K, a.part, a.accumulate and a.gated are set.

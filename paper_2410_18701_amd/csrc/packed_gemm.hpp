@@ -19,8 +19,9 @@
 // Three kernels, chosen by the rows (packed_gemm_plan in gemm_plan.hpp):
 //  * up to 8 rows, row_gemm_kernel: no barrier, no LDS until the end; where it
 //    is not the faster one, skinny_gemm_kernel;
-//  * 9 to 64 rows, plain products, skinny_gemm_kernel: one slice per wave;
-//  * 9 to 64 rows with the gated activation, and everything past 64 rows,
+//  * 9 to 64 rows, skinny_gemm_kernel: one slice per wave; with the gated
+//    activation only where its workgroups make one round;
+//  * past 64 rows, and with the gated activation from 9 rows otherwise,
 //    tile_gemm_kernel: one to three slices per wave, the LDS reads of the
 //    activations pipelined ahead of the matrix operations.
 // Unsplit, the kernels that a row count may take add along k in the same order
@@ -218,7 +219,7 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) row_gemm_kernel(const Gemm
     gemm_store(a, c16, n, acc[0]);
 }
 
-// ------------ 9 to 64 rows, ungated, and up to 8 rows where it is faster --
+// ------------------------- 9 to 64 rows, and up to 8 where it is faster --
 // A wave owns one slice (four per workgroup; gated: two gate slices and their
 // up slices), the workgroup all the rows.  The
 // activation rows are staged in LDS per batch of four blocks, each row padded
@@ -364,7 +365,7 @@ __global__ void __launch_bounds__(kWave * kGemmWaves) skinny_gemm_kernel(const G
   }
 }
 
-// -------------------------------- past 64 rows, and 9 to 64 rows gated --
+// ------------------------- past 64 rows, and gated from 9 rows if faster --
 // The (slice group, row chunk) of a workgroup.  One chunk: the group is the
 // workgroup index.  Several: workgroups are dealt to the GPU's eight XCDs in
 // turn (index mod 8), so the chunks of one group go to indices 8 apart -- the

@@ -212,17 +212,8 @@ def test_packed_products_edges(rows, in_dim, out_dim, ws):
     g.close()
 
 
-# Up to 8 rows either of two kernels, by the sizes: the choice for a gated product
-# and for the plain one of the same weight need not be the same, the bits are
-# (12288 x 4096 at 1 row and 2048 x 600 take one each).  The products that split
-# along k: ranges of the kernel with a workgroup per slice (few outputs, long k),
-# and two ranges of the staged one (5200 x 3080).
-@pytest.mark.parametrize("rows,F,in_dim,kinds", [
-    (1, 6144, 4096, (G.ROW, G.STAGED)), (3, 1024, 600, (G.ROW, G.STAGED)), (8, 5120, 520, (G.STAGED, G.STAGED)),
-    (7, 48, 200, (G.STAGED, G.STAGED)), (8, 8176, 2056, (G.STAGED, G.STAGED)), (2, 16384, 72, (G.STAGED, G.STAGED)),
-    (8, 11008, 1032, (G.STAGED, G.STAGED)), (5, 1040, 1096, (G.ROW, G.ROW))])
-def test_kernels_of_up_to_8_rows_agree(rows, F, in_dim, kinds):
-    assert (G.plan(rows, 2 * F, in_dim, False, 0).kind, G.plan(rows, 2 * F, in_dim, True).kind) == kinds
+def _gated_against_plain(rows, F, in_dim):
+    """linear_packed_silu bit for bit linear_packed without a workspace then silu_mul, and the product against the oracle."""
     rng = np.random.default_rng(rows + F + in_dim)
     xb, wb = _bits(rng, (rows, in_dim)), _bits(rng, (2 * F, in_dim), round(np.log2(in_dim) / 2))
     g = PL.Gemm(ws_bytes=0)
@@ -236,6 +227,32 @@ def test_kernels_of_up_to_8_rows_agree(rows, F, in_dim, kinds):
     assert np.array_equal(parity.host_bits(out), parity.host_bits(ref)), "fused against linear_packed + silu_mul"
     _close(_val(gu), LL.linear(O.widen(xb, O.BF16), O.widen(wb, O.BF16)), what="gate_up")
     g.close()
+
+
+# Up to 8 rows either of two kernels, by the sizes: the choice for a gated product
+# and for the plain one of the same weight need not be the same, the bits are
+# (12288 x 4096 at 1 row and 2048 x 600 take one each).  The products that split
+# along k: ranges of the kernel with a workgroup per slice (few outputs, long k),
+# and two ranges of the staged one (5200 x 3080).
+@pytest.mark.parametrize("rows,F,in_dim,kinds", [
+    (1, 6144, 4096, (G.ROW, G.STAGED)), (3, 1024, 600, (G.ROW, G.STAGED)), (8, 5120, 520, (G.STAGED, G.STAGED)),
+    (7, 48, 200, (G.STAGED, G.STAGED)), (8, 8176, 2056, (G.STAGED, G.STAGED)), (2, 16384, 72, (G.STAGED, G.STAGED)),
+    (8, 11008, 1032, (G.STAGED, G.STAGED)), (5, 1040, 1096, (G.ROW, G.ROW))])
+def test_kernels_of_up_to_8_rows_agree(rows, F, in_dim, kinds):
+    assert (G.plan(rows, 2 * F, in_dim, False, 0).kind, G.plan(rows, 2 * F, in_dim, True).kind) == kinds
+    _gated_against_plain(rows, F, in_dim)
+
+
+# The gated product at 9 to 64 rows: the staged kernel at one to four row tiles with
+# a last gate slice alone, and the tile kernel with one and two slices per wave, the
+# last workgroup with one gate slice of its four.
+@pytest.mark.parametrize("rows,F,in_dim,kind,ns", [
+    (9, 1040, 1032, G.STAGED, 1), (17, 48, 2056, G.STAGED, 1), (48, 528, 1096, G.STAGED, 1), (64, 48, 4104, G.STAGED, 1),
+    (32, 11024, 1000, G.TILE, 1), (33, 11024, 1000, G.TILE, 2), (64, 11024, 1096, G.TILE, 2), (17, 8240, 6408, G.TILE, 2), (10, 11024, 8, G.TILE, 1)])
+def test_gated_kernels_of_9_to_64_rows(rows, F, in_dim, kind, ns):
+    p = G.plan(rows, 2 * F, in_dim, True)
+    assert (p.kind, p.ns) == (kind, ns)
+    _gated_against_plain(rows, F, in_dim)
 
 
 @pytest.mark.parametrize("rows,out_dim,in_dim,kind,splits", [
