@@ -19,10 +19,11 @@ struct GemmPlan {
   int32_t tc, splits;   // 32-wide blocks per split, splits along k
 };
 
-// The tile_gemm_kernel forms that exist: up to 64 rows gated products only, of
-// one or two slices per wave and one row chunk.
+// The tile_gemm_kernel forms that exist: with one row chunk of up to 64 rows
+// gated products only, of one or two slices per wave; chunks of 48 rows or more
+// otherwise.
 constexpr bool tile_gemm_built(int32_t mt, int32_t ns, int32_t chunks, bool gated) {
-  return mt >= 1 && mt <= 8 && ns >= 1 && (mt > 4 ? ns <= 3 : gated && ns <= 2 && chunks == 1);
+  return mt >= 1 && mt <= 8 && ns >= 1 && ns <= 3 && (mt > 4 || (chunks > 1 ? mt > 2 : gated && ns <= 2));
 }
 
 // Up to 8 rows: row_gemm_kernel (a workgroup per slice, k over its four waves)
@@ -81,11 +82,12 @@ inline int32_t row_splits(int32_t slices, int32_t kt, int32_t max_splits) {
 }
 
 // The plan of a product of `rows` rows with `slices` 16-row weight slices
-// (gated: of gate slices, each with its up slice) of kt blocks, `max_splits`
-// the most the workspace holds partial sums for.  The plan depends on the
+// (gated: of gate slices, each with its up slice), `max_splits` the most the
+// workspace holds partial sums for.  The plan depends on the
 // sizes alone.  Any kernel it may take for a row count sums an unsplit product
 // in the same order, gated or not, so the choice never changes its bits.
-inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t kt, bool gated, int32_t max_splits) {
+inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t in_dim, bool gated, int32_t max_splits) {
+  const int32_t kt = (in_dim + 31) / 32;   // 32-wide blocks
   GemmPlan p;
   p.chunks = 1;
   p.splits = 1;
@@ -144,32 +146,46 @@ inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t kt, bool 
       }
     }
   } else {
-    // The tile (slices per wave) and the split that the measured costs favour:
-    // a workgroup's step of 64 along k takes its CU about (2 mt + 8 ns) KB of
-    // loads at 0.022 us a KB, the workgroups run in rounds of 256, and a split
-    // costs a launch (4 us) and writes and reads its partial sums (5 TB/s).
-    // llama2-7b, modelled / measured us: QKV at 256 rows 3 slices, 2 splits
-    // 43 / 42 (2 slices, 1 split 46 / 46), down at 256 rows 2 slices, 4 splits
-    // 41 / 40 (3 and 5: 44 / 45), QKV at 128 rows 2 and 2 31 / 33 (1 and 1
-    // 34 / 34), gate/up at 128 rows 2 slices 45 / 51 (3: 56 / 62, 1: 67 / 61).
+    // The row chunks, slices per wave and split that the measured costs favour.
+    // The workgroups run in rounds of one per CU: 256, or 32 per XCD where the
+    // chunks of a group share one.  A workgroup takes 0.13 mt ns us for its start
+    // and outputs and, for each step of 64 along k (2 mt KB of activations, 8 ns KB
+    // of weights), 0.021 + 0.032 mt + 0.112 ns, with rows of x that do not start on
+    // 128 bytes 0.041 mt, and 0.02 more where chunks share the weights; a split
+    // costs a launch, 0.37 us per range and its partial sums (at 10 TB/s: they stay
+    // in the caches).  Fitted to 60,000 launches (65 to 256 rows, 192 to 32,768
+    // outputs of 64 to 16,384, all chunks, slices and splits), of which the choice
+    // is within 1.1% of the best on average.  us, chunks of up to 128 rows and up
+    // to 8 splits / this: 128 rows 1024 x 16384 22.8 / 19.1, 512 x 16384 21.8 /
+    // 17.8, 256 rows 1536 x 4096 19.3 / 16.3, 256 rows 2592 x 8368 43.9 / 29.8,
+    // gated 160 rows 10240 x 4096 39.7 / 34.5.
     p.kind = kTileGemm;
-    p.chunks = rows > 128 ? 2 : 1;
-    p.mt = (rows + 16 * p.chunks - 1) / (16 * p.chunks);
-    double best = 0;
-    p.ns = 0;
-    const int32_t n_out = 16 * slices;
-    for (int32_t ns = 1; ns <= 3; ++ns) {
-      const int32_t per = gated ? 2 * ns : 4 * ns, groups = (slices + per - 1) / per;
-      for (int32_t s = 1; s <= (gated ? 1 : std::min(8, std::max(1, max_splits))); ++s) {
-        const int32_t tc = (kt + s - 1) / s, sn = (kt + tc - 1) / tc;
-        const int64_t rounds = ((int64_t)groups * p.chunks * sn + 255) / 256;
-        const double us = 0.022 * rounds * ((tc + 1) / 2) * (2 * p.mt + 8 * ns) +
-                          (sn > 1 ? 4 + 8e-6 / 5 * sn * rows * (double)n_out : 0);
-        if (p.ns == 0 || us < best) {
-          best = us;
-          p.ns = ns;
-          p.groups = groups;
-          p.splits = sn;
+    double best = -1;
+    const double n_out = 16.0 * slices * rows, x_cost = in_dim % 64 ? 0.041 : 0.032;
+    // A step or two of k: the launch is its start and its outputs, and many small
+    // workgroups overlap them: 256 rows 16384 x 64 8.3 / 6.8 us.
+    const bool short_k = kt <= 4 && slices < 1 << 20;
+    const int32_t c_lo = short_k ? (rows + 63) / 64 : (rows + 127) / 128, c_hi = short_k ? c_lo : (rows + 47) / 48;
+    for (int32_t c = c_lo; c <= c_hi; ++c) {
+      const int32_t mt = (rows + 16 * c - 1) / (16 * c);
+      if ((c - 1) * mt * 16 >= rows) continue;   // the last chunk would be empty
+      for (int32_t ns = 1; ns <= (short_k ? 1 : 3); ++ns) {
+        const int32_t per = gated ? 2 * ns : kGemmWaves * ns, groups = (slices + per - 1) / per;
+        for (const int32_t s : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20}) {
+          if (s > 1 && (gated || short_k || s > max_splits || s > kt / 4 || (int64_t)groups * c * s > 768)) break;
+          const int32_t tc = (kt + s - 1) / s, sn = (kt + tc - 1) / tc;
+          const int64_t rounds = c == 1 ? ((int64_t)groups * sn + 255) / 256 : ((int64_t)(groups + 7) / 8 * c * sn + 31) / 32;
+          const double step = (c > 1 ? 0.041 : 0.021) + x_cost * mt + 0.112 * ns;
+          const double us = rounds * (0.13 * mt * ns + (tc + 1) / 2 * step) +
+                            (sn > 1 ? 1.6 + 0.37 * sn + 8.3e-7 * sn * n_out : 0);
+          if (best < 0 || us < best) {
+            best = us;
+            p.chunks = c;
+            p.mt = mt;
+            p.ns = ns;
+            p.groups = groups;
+            p.splits = sn;
+          }
         }
       }
     }

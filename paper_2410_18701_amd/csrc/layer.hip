@@ -80,7 +80,7 @@ int32_t launch_packed_gemm(baton::GemmArgs& a, int32_t max_splits, hipStream_t s
   const bool gated = a.gated > 0;
   a.kt = (a.K + 31) / 32;
   const baton::GemmPlan p =
-      baton::packed_gemm_plan(a.rows, gated ? a.gated / 16 : (a.N + 15) / 16, a.kt, gated, max_splits);
+      baton::packed_gemm_plan(a.rows, gated ? a.gated / 16 : (a.N + 15) / 16, a.K, gated, max_splits);
   a.chunks = p.chunks;
   a.groups = p.groups;
   a.tc = p.tc;

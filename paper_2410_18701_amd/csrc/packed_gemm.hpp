@@ -45,7 +45,7 @@ struct GemmArgs {
   uint16_t* y;           // [rows][N]
   float* part;           // [S][rows][N] fp32, when S > 1
   int32_t rows, N, K;    // rows <= 256
-  int32_t chunks;        // row chunks (tile_gemm_kernel past 128 rows: 2), or 1
+  int32_t chunks;        // row chunks (tile_gemm_kernel past 64 rows), or 1
   int32_t groups;        // slice groups (workgroups per chunk)
   int32_t kt;            // blocks per slice, ceil(K / 32)
   int32_t tc;            // blocks per split

@@ -10,8 +10,8 @@ import tempfile
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_18701_amd", "csrc")
 SHIM = """
 #include "gemm_plan.hpp"
-extern "C" void plan(int rows, int slices, int kt, int gated, int max_splits, int* o) {
-  const baton::GemmPlan p = baton::packed_gemm_plan(rows, slices, kt, gated != 0, max_splits);
+extern "C" void plan(int rows, int slices, int in_dim, int gated, int max_splits, int* o) {
+  const baton::GemmPlan p = baton::packed_gemm_plan(rows, slices, in_dim, gated != 0, max_splits);
   const int v[] = {p.kind, p.mt, p.ns, p.chunks, p.groups, p.tc, p.splits};
   for (int i = 0; i < 7; ++i) o[i] = v[i];
 }
@@ -39,7 +39,7 @@ def plan(rows, out_dim, in_dim, gated=False, ws_bytes=32 << 20):
     o = (ctypes.c_int * 7)()
     slices = out_dim // 32 if gated else -(-out_dim // 16)
     splits = 1 if gated or not ws_bytes else min(ws_bytes // (4 * rows * out_dim), 1024)
-    lib().plan(rows, slices, -(-in_dim // 32), int(gated), splits, o)
+    lib().plan(rows, slices, in_dim, int(gated), splits, o)
     return Plan(*o)
 
 

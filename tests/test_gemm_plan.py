@@ -37,10 +37,10 @@ def test_every_plan_covers_the_product(gated):
 
 def test_forms_that_do_not_exist_are_known():
     """The launcher asks the same predicate and returns an error for a form that was not built."""
-    for mt, ns, chunks, gated in [(4, 1, 1, False), (1, 1, 1, False), (1, 1, 2, True), (2, 3, 1, True), (9, 1, 2, True),
+    for mt, ns, chunks, gated in [(4, 1, 1, False), (1, 1, 1, False), (1, 1, 2, True), (2, 1, 2, False), (2, 3, 1, True), (9, 1, 2, True),
                                   (5, 4, 1, False), (0, 1, 1, True), (8, 0, 1, True)]:
         assert not G.tile_built(mt, ns, chunks, gated), (mt, ns, chunks, gated)
-    assert G.tile_built(8, 3, 2, False) and G.tile_built(4, 2, 1, True) and G.tile_built(5, 1, 1, False)
+    assert G.tile_built(8, 3, 2, False) and G.tile_built(3, 3, 2, False) and G.tile_built(4, 2, 1, True) and G.tile_built(5, 1, 1, False)
 
 
 # (rows, out, in, gated, kind, least workgroups): sizes at which the wrong kernel or
@@ -65,6 +65,17 @@ def test_up_to_8_rows(rows, out_dim, in_dim, gated, kind, least):
     (64, 22016, 4096, G.TILE)])
 def test_gated_9_to_64_rows(rows, out_dim, in_dim, kind):
     assert G.plan(rows, out_dim, in_dim, True).kind == kind
+
+
+# Past 64 rows: the plan of chunks of up to 128 rows and 8 splits left most of the GPU
+# idle where outputs are few (64 to 160 workgroups), and 160 rows in two chunks took
+# one and a quarter rounds where three chunks make one.
+@pytest.mark.parametrize("rows,out_dim,in_dim,gated,least,most", [
+    (128, 512, 16384, False, 120, 256), (65, 512, 11008, False, 96, 256), (128, 1024, 16384, False, 160, 256),
+    (256, 512, 16384, False, 160, 256), (256, 1024, 8192, True, 48, 256), (160, 10240, 4096, True, 200, 256)])
+def test_past_64_rows_fills_the_gpu(rows, out_dim, in_dim, gated, least, most):
+    p = G.plan(rows, out_dim, in_dim, gated)
+    assert least <= p.groups * p.chunks * p.splits <= most, p
 
 
 def test_launches_stay_below_2_to_the_32_threads():
