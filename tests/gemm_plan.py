@@ -20,6 +20,7 @@ extern "C" int tile_built(int mt, int ns, int chunks, int gated) {
 }
 """
 ROW, STAGED, TILE = 0, 1, 2
+kWaves = 4   # per workgroup
 Plan = collections.namedtuple("Plan", "kind mt ns chunks groups tc splits")
 
 
@@ -45,3 +46,26 @@ def plan(rows, out_dim, in_dim, gated=False, ws_bytes=32 << 20):
 
 def tile_built(mt, ns, chunks, gated):
     return bool(lib().tile_built(mt, ns, chunks, int(gated)))
+
+
+# (rows, out, in) whose plans past 64 rows -- plain without a workspace, plain with one,
+# gated where out allows -- reach every tile form the rule can choose, with outputs that
+# leave part of a wave's slices and of a workgroup empty.
+PAST_64 = [
+    (65, 32, 136), (65, 8480, 136), (65, 16448, 2056), (65, 32896, 136), (81, 8480, 136), (81, 16448, 2056),
+    (81, 24608, 136), (81, 32896, 136), (97, 8256, 136), (97, 10280, 136), (97, 10400, 136), (97, 16448, 136),
+    (97, 16448, 2056), (97, 32896, 136), (113, 5128, 2056), (113, 10272, 136), (113, 13664, 192), (113, 24608, 136),
+    (113, 32896, 136), (129, 5344, 136), (129, 16448, 136), (150, 4128, 2056), (161, 12512, 136), (161, 16448, 136),
+    (192, 5408, 192), (193, 6240, 136), (193, 9280, 136), (193, 12512, 136), (193, 16448, 136), (225, 16448, 136),
+    (244, 1040, 4104), (256, 1032, 2056), (256, 12512, 136), (256, 22016, 72)]
+
+
+def past_64(rows, out_dim, in_dim):
+    """The tile forms (mt, ns, several chunks, gated) that the product's three calls take and
+    that leave part of a workgroup empty."""
+    forms = set()
+    for gated, ws in [(False, 0), (False, 32 << 20)] + [(True, 0)] * (out_dim % 32 == 0):
+        p = plan(rows, out_dim, in_dim, gated, ws)
+        if (out_dim // 32 if gated else -(-out_dim // 16)) % ((2 if gated else kWaves) * p.ns):
+            forms.add((p.mt, p.ns, p.chunks > 1, gated))
+    return forms

@@ -78,6 +78,16 @@ def test_past_64_rows_fills_the_gpu(rows, out_dim, in_dim, gated, least, most):
     assert least <= p.groups * p.chunks * p.splits <= most, p
 
 
+def test_the_edge_products_reach_every_tile_form():
+    """Guards the GPU tests of G.PAST_64: a change of the rule that drops a form from them fails here."""
+    forms = set().union(*(G.past_64(*a) for a in G.PAST_64))
+    every = {(mt, ns, chunks, gated) for mt in range(3, 9) for ns in (1, 2, 3) for chunks in (False, True)
+             for gated in (False, True) if chunks or mt > 4}
+    # one slice per wave of 128-row chunks, gated: four chunks of 64 rows are always the cheaper choice
+    assert every - forms == {(8, 1, True, True)}
+    assert any(G.plan(*a).splits > 1 and G.plan(*a).chunks > 1 for a in G.PAST_64)
+
+
 def test_launches_stay_below_2_to_the_32_threads():
     """Weights of 2^28 outputs and more, which a workgroup per slice cannot launch."""
     for rows in (1, 8, 9, 64, 65, 256):

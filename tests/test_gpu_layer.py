@@ -87,9 +87,9 @@ def _pack_reference(wb):
 # (rows, out_dim, in_dim, workspace bytes): one split along in_dim (many
 # outputs, or no workspace), several splits and their reduction (64 x 4096 x
 # 4096, 8 x 4096 x 11008), a partial 16-row slice and a column tail shorter
-# than 32 (17 x 1000 x 1000), every group of 16 rows; past 64 rows, chunks of
-# 64 (128 and 256 rows at llama2-7b's shapes, a partial last chunk at 100 and
-# 200 rows, with and without splits).
+# than 32 (17 x 1000 x 1000), every group of 16 rows; past 64 rows, one or more
+# chunks (128 and 256 rows at llama2-7b's shapes, a partial last row tile at 100
+# and 200 rows, with and without splits).
 @pytest.mark.parametrize("rows,out_dim,in_dim,ws", [
     (1, 64, 64, 32 << 20), (5, 520, 136, 32 << 20), (64, 4096, 4096, 32 << 20), (8, 4096, 11008, 32 << 20),
     (17, 1000, 1000, 32 << 20), (33, 12288, 4096, 32 << 20), (64, 4096, 4096, 0), (48, 22016, 4096, 32 << 20),
@@ -176,40 +176,59 @@ def test_linear_packed_silu(rows, F, in_dim):
     g0.close()
 
 
-# The products' kernels at the edges of their ranges and tiles: 1 and 8 rows
-# (the kernel without staging), 9 and 64 (staged rows), 65 .. 256 (one to two
-# chunks of five to eight row tiles), k of one 16-byte piece, of an odd number
-# of 32-wide blocks and with a tail shorter than 32, outputs that leave part of
-# a slice, of a wave's slices and of a workgroup empty, with and without splits
-# along k.  The rows of x past the last one and the outputs past the last row
-# are NaN: neither may be read into a result or written.
-@pytest.mark.parametrize("in_dim,out_dim,ws", [(8, 32, 0), (72, 96, 32 << 20), (200, 1056, 32 << 20),
-                                               (2056, 416, 32 << 20), (4104, 32, 32 << 20)])
-@pytest.mark.parametrize("rows", [1, 7, 8, 9, 16, 33, 64, 65, 80, 81, 112, 128, 129, 161, 192, 225, 256])
-def test_packed_products_edges(rows, in_dim, out_dim, ws):
+def _packed_products(rows, in_dim, out_dim, ws):
+    """linear_packed, with accumulate, and linear_packed_silu (out_dim in whole pairs of
+    slices) against the oracle, in buffers of NaN past the last row."""
     rng = np.random.default_rng(rows * 131 + in_dim + out_dim)
     k = round(np.log2(in_dim) / 2)
     xb, wb = _bits(rng, (rows, in_dim)), _bits(rng, (out_dim, in_dim), k)
     g = PL.Gemm(ws_bytes=ws)
     wp = g.pack(_dev(wb))
     nan = lambda n: torch.full((rows + 16, n), float("nan"), dtype=torch.bfloat16, device="cuda")
-    xp, yp, ap = nan(in_dim), nan(out_dim), nan(out_dim // 2)
+    F = out_dim // 2 if out_dim % 32 == 0 else 0
+    xp, yp, ap = nan(in_dim), nan(out_dim), nan(F)
     xp[:rows] = _dev(xb)
     g.linear_packed(xp[:rows], wp, yp[:rows])
-    g.linear_packed_silu(xp[:rows], wp, ap[:rows])
+    if F:
+        g.linear_packed_silu(xp[:rows], wp, ap[:rows])
     y2 = yp.clone()
     g.linear_packed(xp[:rows], wp, y2[:rows], accumulate=True)
     torch.cuda.synchronize()
     want = LL.linear(O.widen(xb, O.BF16), O.widen(wb, O.BF16))
     _close(_val(yp[:rows].contiguous()), want, what="linear_packed")
     _close(_val(y2[:rows].contiguous()), _val(yp[:rows].contiguous()) + want, what="accumulate")
-    F = out_dim // 2
-    # gate and up are rounded to bf16 before the activation: half a unit of each
-    # (2^-9) and of the result, and the activation's slope (at most 1.1 times |gate|'s)
-    _close(_val(ap[:rows].contiguous()), LL.silu(want[:, :F]) * want[:, F:], rel=2.0 ** -6, atol=4e-3, what="gated")
+    if F:
+        # gate and up are rounded to bf16 before the activation: half a unit of each
+        # (2^-9) and of the result, and the activation's slope (at most 1.1 times |gate|'s)
+        _close(_val(ap[:rows].contiguous()), LL.silu(want[:, :F]) * want[:, F:], rel=2.0 ** -6, atol=4e-3, what="gated")
     for t in (yp, y2, ap):
         assert torch.isnan(t[rows:]).all(), "written past the last row"
     g.close()
+
+
+# The products' kernels at the edges of their ranges and tiles: 1 and 8 rows
+# (a workgroup per slice or staged rows), 9 and 64 (staged rows), 65 .. 256 (row
+# chunks of three to eight tiles, one slice per wave: these products are too small
+# for the rule to take more), k of one 16-byte piece, of an odd number of 32-wide
+# blocks and with a tail shorter than 32, outputs that leave part of a slice and of
+# a workgroup empty, with and without splits along k.  The rows of x past the last
+# one and the outputs past the last row are NaN: neither may be read into a result
+# or written.
+@pytest.mark.parametrize("in_dim,out_dim,ws", [(8, 32, 0), (72, 96, 32 << 20), (200, 1056, 32 << 20),
+                                               (2056, 416, 32 << 20), (4104, 32, 32 << 20)])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 16, 33, 64, 65, 80, 81, 112, 128, 129, 161, 192, 225, 256])
+def test_packed_products_edges(rows, in_dim, out_dim, ws):
+    _packed_products(rows, in_dim, out_dim, ws)
+
+
+# Past 64 rows, every tile form the rule can choose -- three to eight row tiles, one to
+# three slices per wave, one chunk or several, gated or not, with splits or without --
+# at outputs that leave part of a wave's slices, of a workgroup and, with several chunks,
+# of the grid empty.
+@pytest.mark.parametrize("ws", [0, 32 << 20])
+@pytest.mark.parametrize("rows,out_dim,in_dim", G.PAST_64)
+def test_tile_forms(rows, out_dim, in_dim, ws):
+    _packed_products(rows, in_dim, out_dim, ws)
 
 
 def _gated_against_plain(rows, F, in_dim):
@@ -369,7 +388,7 @@ def test_layers_small_model():
 
 
 def test_layers_small_model_128_slots():
-    """Past 64 slots every projection takes its rows in chunks of 64."""
+    """Past 64 slots the projections take the tile kernel."""
     m = M.ModelShape(256, 4, 2, 64, 512)
     lens = [(7 * b) % 50 + 1 for b in range(128)]
     ops = [("embed", list(range(128)), lens, list(range(128))), ("step",),
