@@ -256,18 +256,17 @@ void launch_prefill_g(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s
 
 template <int D>
 void launch_prefill_f32(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s) {
-  // 32 positions per workgroup where 16 would give more workgroups than run at
-  // once (by the kernel's registers four a CU at head_dim 64, two at 128);
-  // below that 16 shorten the launch.  16 / 32 positions, us: 8 heads of 64,
-  // 1024 tokens (512 workgroups) 27 / 35; 32 heads of 128, 300 tokens (608)
-  // 28 / 26, 1024 tokens (2048) 156 / 137.
   prefill_tiles(c, a, 16);
-  if (a.n_attn > 256 * (D == 64 ? 4 : 2)) {
-    prefill_tiles(c, a, 32);
-    hipLaunchKernelGGL((baton::prefill_f32_kernel<D, 2>), dim3(a.n_attn), dim3(256), 0, s, a);
-  } else {
-    hipLaunchKernelGGL((baton::prefill_f32_kernel<D, 1>), dim3(a.n_attn), dim3(256), 0, s, a);
-  }
+  // At head_dim 128 two workgroups fit a CU.  With up to two per CU in all and
+  // long prompts, a CU that gets two of the longest tiles at once ends last; LDS
+  // that only one workgroup fits (33 KB of its own) lets the longest run alone and
+  // the short ones follow.  us, two / one: 8 heads of 700 tokens (352 workgroups)
+  // 31.2 / 27.6, 4 of 2048 (512) 82.8 / 71.3; but 32 heads of 256 (512) 19.0 / 22.3,
+  // 16 of 512 (512) 28.7 / 29.3, 8 of 1200 (600) 55.0 / 61.8.
+  int32_t longest = 0;
+  for (int32_t i = 0; i < a.n_ins; ++i) longest = std::max(longest, a.plen[i]);
+  const uint32_t lds = D == 128 && a.n_attn > 256 && a.n_attn <= 512 && longest >= 600 ? 50 << 10 : 0;
+  hipLaunchKernelGGL(baton::prefill_f32_kernel<D>, dim3(a.n_attn), dim3(256), lds, s, a);
 }
 
 template <int D>

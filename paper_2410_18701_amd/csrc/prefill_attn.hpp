@@ -94,14 +94,19 @@ __device__ __forceinline__ void prefill_append(const PrefillArgs& a, int b, int 
 }
 
 // fp32, on the fp32 matrix operation (v_mfma_f32_16x16x4_f32: fp32 products
-// and sums, so the same precision as the vector ALUs).  A workgroup of four
-// waves takes 16 QG positions of one query head; wave w takes every fourth
+// and sums).  A workgroup of four
+// waves takes 16 positions of one query head; wave w takes every fourth
 // block of 16 keys from block w on, and the waves' softmax states merge through
 // LDS at the end.  What bounds it is, for short prompts, the chain of blocks a
 // wave walks -- hence the split of the keys over the waves instead of the
 // positions, and no barrier on the way -- and for long ones the loads of K in
-// the operand's layout (16 rows of 64 bytes, a quarter of the L1's rate), which
-// QG = 2 halves per matrix operation.
+// the operand's layout (16 rows of 64 bytes, a quarter of the L1's rate).  The
+// registers are capped for four workgroups a CU at head_dim 64 (123 used) and two
+// at 128 (236): the compiler then gives the operations' results to the vector ALUs
+// directly, where without a cap it took 164 and 284, accumulators among them, that
+// every addition had to read back.  (32 positions per workgroup, which halve the
+// loads per operation but run one or two workgroups a CU, take 1.05 to 2.0 times
+// as long at every size measured: 3 to 19,456 workgroups, prompts of 20 to 4,096.)
 //  * QK^T: A = 16 key rows, B = 16 positions.  The contraction's order is free,
 //    so step (i, e) takes element e of the 16-byte vectors at 16 i + 4 (l / 16):
 //    both operands are loaded 16 bytes per lane.  Lane l, register r holds the
@@ -111,12 +116,13 @@ __device__ __forceinline__ void prefill_append(const PrefillArgs& a, int b, int 
 //    the columns 64 h + 4 c + e, c < 16: the V rows are loaded whole, 16 bytes
 //    per lane.  Lane l holds columns 64 h + 16 (l / 16) + 4 r + e of position
 //    l % 16: its outputs are 16-byte vectors over e.
-// One prompt, 8 query heads over 4 kv-heads, head_dim 64, us, against a kernel
-// that walked the keys one at a time on the vector ALUs: 40 tokens 16.4 -> 5.4, 300
-// 103.5 -> 9.8, 1024 359 -> 27; 32 heads of 128: 300 tokens 111 -> 26, 1024
-// 652 -> 137 (63 TFLOP/s of the matrix operation's 157).
-template <int D, int QG>
-__global__ void __launch_bounds__(256) prefill_f32_kernel(const PrefillArgs a) {
+// us per layer, one prompt, 8 query heads over 4 kv-heads, head_dim 64, against a
+// kernel that walked the keys one at a time on the vector ALUs: 40 tokens 14.4 ->
+// 6.4, 300 81 -> 10.5, 1024 276 -> 27; 32 heads of 128: 300 tokens 93 -> 24.6, 1024
+// 550 -> 127 (68 TFLOP/s of the matrix operation's 157).
+template <int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+prefill_f32_kernel(const PrefillArgs a) {
   constexpr int VPT = D / 4, DI = D / 16, DH = D / 64, NW = 4;
   __shared__ __attribute__((aligned(16))) f32x4 so[NW][DH * 4][kWave];
   __shared__ float sm[NW][16], sl[NW][16];
@@ -129,34 +135,26 @@ __global__ void __launch_bounds__(256) prefill_f32_kernel(const PrefillArgs a) {
   const int nkv = a.n_kv_heads, nq = a.n_attn / a.n_tiles, group = nq / nkv, h = hq / group;
   const int b = a.slot[ins];
   const int32_t p = a.plen[ins];
-  const int32_t i0 = tile * 16 * QG;
+  const int32_t i0 = tile * 16;
   const int64_t row0 = (int64_t)b * a.T + (a.T - p);
   const u32x4* kin = reinterpret_cast<const u32x4*>(a.knew);
   const u32x4* vin = reinterpret_cast<const u32x4*>(a.vnew);
 
   // The positions as B operands, pre-scaled; positions past the prompt: zeros.
-  f32x4 qf[QG][DI];
+  const int32_t qi = i0 + c16;
+  f32x4 qf[DI];
 #pragma unroll
-  for (int gq = 0; gq < QG; ++gq) {
-    const int32_t qi = i0 + 16 * gq + c16;
-#pragma unroll
-    for (int i = 0; i < DI; ++i) {
-      const u32x4 x = qi < p ? reinterpret_cast<const u32x4*>(a.q)[((row0 + qi) * nq + hq) * VPT + 4 * i + g4]
-                             : u32x4{0, 0, 0, 0};
-      qf[gq][i] = __builtin_bit_cast(f32x4, x) * a.qscale;
-    }
+  for (int i = 0; i < DI; ++i) {
+    const u32x4 x = qi < p ? reinterpret_cast<const u32x4*>(a.q)[((row0 + qi) * nq + hq) * VPT + 4 * i + g4]
+                           : u32x4{0, 0, 0, 0};
+    qf[i] = __builtin_bit_cast(f32x4, x) * a.qscale;
   }
-  float m[QG], l[QG];
-  f32x4 o[QG][DH][4];
+  float m = -INFINITY, l = 0.f;
+  f32x4 o[DH][4];
 #pragma unroll
-  for (int gq = 0; gq < QG; ++gq) {
-    m[gq] = -INFINITY;
-    l[gq] = 0.f;
+  for (int hh = 0; hh < DH; ++hh)
 #pragma unroll
-    for (int hh = 0; hh < DH; ++hh)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[gq][hh][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+    for (int e = 0; e < 4; ++e) o[hh][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   // The prompt's keys and values of head h as raw buffers; a token past the
   // prompt gets an offset beyond the range, which loads zeros.
   const uint32_t tok_bytes = (uint32_t)nkv * VPT * 16;
@@ -183,64 +181,73 @@ __global__ void __launch_bounds__(256) prefill_f32_kernel(const PrefillArgs a) {
       for (int hh = 0; hh < DH; ++hh) vf[r][hh] = load(rv, off + 256u * hh);
     }
   };
-  const int32_t last = min(i0 + 16 * QG, p) - 1;   // the last position, and the last key it sees
+  const int32_t last = min(i0 + 16, p) - 1;   // the last position, and the last key it sees
   int32_t kb = 16 * w;
   if (kb <= last) {
     load_k(kb);
     load_v(kb);
   }
   for (; kb <= last; kb += 16 * NW) {               // wave-uniform
-    // Partial sums over four vectors each (by element, and by halves at
-    // head_dim 128), added as a tree: chains as short in rounding as a lane's
-    // own sum of four on the vector ALUs, and short in latency.
-    constexpr int NP = DI;                          // 4 (head_dim 64) or 8
-    f32x4 sp[QG][NP], s[QG];
+    // Every matrix operation starts from zero, four products, and the 4 DI of
+    // them are added as a tree: a score's rounding error is that of a lane's own
+    // sum of four products and a tree over the lanes (2-norm against float64 where
+    // scores dominate, of that: chains of four operations 1.04 to 1.24, of two 1.00
+    // to 1.10, this 0.97 to 1.03).  Eight operations at a time, with the additions of
+    // the eight before placed between them, in the operations' shadow; left alone
+    // the compiler issues all of them first and spills.
+    constexpr int NE = DI / 2;                      // eights of a score's operations
+    f32x4 pr[2][8], part[NE];
 #pragma unroll
-    for (int gq = 0; gq < QG; ++gq)
+    for (int x = 0; x <= NE; ++x) {
+      if (x < NE) {
 #pragma unroll
-      for (int e = 0; e < NP; ++e) sp[gq][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 8; ++j) {
+          const int i = 2 * x + j / 4;
+          pr[x % 2][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][j % 4], qf[i][j % 4], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        }
+      }
+      if (x > 0) {
+        f32x4(&q)[8] = pr[(x - 1) % 2];
+        f32x4& t = part[x - 1];
+        t = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+        asm volatile("" : "+v"(t));                 // added here, not where the loads of the next keys end the block
+      }
+      if (x > 0 && x < NE) {
 #pragma unroll
-    for (int i = 0; i < DI; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int gq = 0; gq < QG; ++gq)
-          sp[gq][(4 * i + e) % NP] =
-              __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][e], qf[gq][i][e], sp[gq][(4 * i + e) % NP], 0, 0, 0);
-#pragma unroll
-    for (int gq = 0; gq < QG; ++gq) {
-#pragma unroll
-      for (int n = NP / 2; n > 0; n /= 2)
-#pragma unroll
-        for (int e = 0; e < n; ++e) sp[gq][e] += sp[gq][e + n];
-      s[gq] = sp[gq][0];
+        for (int j = 0; j < 8; ++j) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a matrix operation
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // and four vector ones
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int n = NE / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int e = 0; e < n; ++e) part[e] += part[e + n];
+    f32x4 s = part[0];
     const bool more = kb + 16 * NW <= last;
     if (more) load_k(kb + 16 * NW);
+    if (kb + 15 > i0) {                             // some position does not see the whole block
 #pragma unroll
-    for (int gq = 0; gq < QG; ++gq) {
-      const int32_t qi = i0 + 16 * gq + c16;
-      if (kb + 15 > i0 + 16 * gq) {                 // some position does not see the whole block
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s[gq][r] = kb + 4 * g4 + r <= qi ? s[gq][r] : -INFINITY;
-      }
-      const float mx = max_over_groups(fmaxf(fmaxf(s[gq][0], s[gq][1]), fmaxf(s[gq][2], s[gq][3])));
-      const float mn = fmaxf(m[gq], mx);
-      const float ref = mn == -INFINITY ? 0.f : mn;
-      const float alpha = exp2f(m[gq] - ref);       // m = -inf before the first visible key: 0
-      float sum = 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        s[gq][r] = exp2f(s[gq][r] - ref);
-        sum += s[gq][r];
-      }
-      l[gq] = l[gq] * alpha + sum;                  // this lane's keys
-      m[gq] = mn;
-#pragma unroll
-      for (int hh = 0; hh < DH; ++hh)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[gq][hh][e] *= alpha;
+      for (int r = 0; r < 4; ++r) s[r] = kb + 4 * g4 + r <= qi ? s[r] : -INFINITY;
     }
+    const float mx = max_over_groups(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+    const float mn = fmaxf(m, mx);
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float alpha = exp2f(m - ref);             // m = -inf before the first visible key: 0
+    float sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      s[r] = exp2f(s[r] - ref);
+      sum += s[r];
+    }
+    l = l * alpha + sum;                            // this lane's keys
+    m = mn;
+#pragma unroll
+    for (int hh = 0; hh < DH; ++hh)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[hh][e] *= alpha;
     // A weight of 0 does not hide a value that is not finite: where a position
     // may not see the whole block and some value of it is inf or NaN (rare),
     // each position adds its visible keys' values one by one.
@@ -254,22 +261,20 @@ __global__ void __launch_bounds__(256) prefill_f32_kernel(const PrefillArgs a) {
           for (int e = 0; e < 4; ++e) odd = odd || (__float_as_uint(vf[r][hh][e]) & 0x7F800000u) == 0x7F800000u;
     }
     if (__ballot(odd)) {
+      for (int j = 0; j < 16 && kb + j <= last; ++j) {
+        // key j's weight for position c16: register j % 4 of lane group j / 4
+        const float wj = __shfl(j % 4 == 0 ? s[0] : j % 4 == 1 ? s[1] : j % 4 == 2 ? s[2] : s[3],
+                                16 * (j / 4) + c16, kWave);
+        if (kb + j > qi) continue;
 #pragma unroll
-      for (int gq = 0; gq < QG; ++gq)
-        for (int j = 0; j < 16 && kb + j <= last; ++j) {
-          // key j's weight for position c16: register j % 4 of lane group j / 4
-          const float wj = __shfl(j % 4 == 0 ? s[gq][0] : j % 4 == 1 ? s[gq][1] : j % 4 == 2 ? s[gq][2] : s[gq][3],
-                                  16 * (j / 4) + c16, kWave);
-          if (kb + j > i0 + 16 * gq + c16) continue;
+        for (int hh = 0; hh < DH; ++hh)
 #pragma unroll
-          for (int hh = 0; hh < DH; ++hh)
+          for (int r = 0; r < 4; ++r) {
+            const f32x4 v = load(rv, (uint32_t)(kb + j) * tok_bytes + 256u * hh + 64u * g4 + 16u * r);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const f32x4 v = load(rv, (uint32_t)(kb + j) * tok_bytes + 256u * hh + 64u * g4 + 16u * r);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o[gq][hh][e][r] = fmaf(wj, v[e], o[gq][hh][e][r]);
-            }
-        }
+            for (int e = 0; e < 4; ++e) o[hh][e][r] = fmaf(wj, v[e], o[hh][e][r]);
+          }
+      }
     } else {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
@@ -277,52 +282,43 @@ __global__ void __launch_bounds__(256) prefill_f32_kernel(const PrefillArgs a) {
         for (int hh = 0; hh < DH; ++hh)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int gq = 0; gq < QG; ++gq)
-              o[gq][hh][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][hh][e], s[gq][r], o[gq][hh][e], 0, 0, 0);
+            o[hh][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][hh][e], s[r], o[hh][e], 0, 0, 0);
     }
     if (more) load_v(kb + 16 * NW);
   }
-  // Merge the waves, a position group at a time: wave w finishes the vectors
-  // of register r = w.
+  // Merge the waves: wave w finishes the vectors of register r = w.
+  const float lw = sum_over_groups(l);
+  if (g4 == 0) {
+    sm[w][c16] = m;
+    sl[w][c16] = lw;
+  }
 #pragma unroll
-  for (int gq = 0; gq < QG; ++gq) {
-    if (gq > 0) __syncthreads();
-    const float lw = sum_over_groups(l[gq]);
-    if (g4 == 0) {
-      sm[w][c16] = m[gq];
-      sl[w][c16] = lw;
-    }
+  for (int hh = 0; hh < DH; ++hh)
 #pragma unroll
-    for (int hh = 0; hh < DH; ++hh)
+    for (int r = 0; r < 4; ++r) so[w][hh * 4 + r][lane] = f32x4{o[hh][0][r], o[hh][1][r], o[hh][2][r], o[hh][3][r]};
+  __syncthreads();
+  float mm = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        so[w][hh * 4 + r][lane] = f32x4{o[gq][hh][0][r], o[gq][hh][1][r], o[gq][hh][2][r], o[gq][hh][3][r]};
-    __syncthreads();
-    const int32_t qi = i0 + 16 * gq + c16;
-    float mm = -INFINITY;
+  for (int q = 0; q < NW; ++q) mm = fmaxf(mm, sm[q][c16]);
+  float lt = 0.f, f[NW];
 #pragma unroll
-    for (int q = 0; q < NW; ++q) mm = fmaxf(mm, sm[q][c16]);
-    float lt = 0.f, f[NW];
+  for (int q = 0; q < NW; ++q) {
+    const float mq = sm[q][c16];
+    f[q] = mq == -INFINITY ? 0.f : exp2f(mq - mm);
+    lt += f[q] * sl[q][c16];
+  }
+  const float inv = 1.f / lt;
+  if (qi < p) {
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      const float mq = sm[q][c16];
-      f[q] = mq == -INFINITY ? 0.f : exp2f(mq - mm);
-      lt += f[q] * sl[q][c16];
-    }
-    const float inv = 1.f / lt;
-    if (qi < p) {
+    for (int hh = 0; hh < DH; ++hh) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int hh = 0; hh < DH; ++hh) {
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int q = 0; q < NW; ++q) v += so[q][hh * 4 + w][lane] * f[q];
-        v *= inv;
-        reinterpret_cast<f32x4*>(a.out)[((row0 + qi) * nq + hq) * VPT + 16 * hh + 4 * g4 + w] = v;
-      }
+      for (int q = 0; q < NW; ++q) v += so[q][hh * 4 + w][lane] * f[q];
+      v *= inv;
+      reinterpret_cast<f32x4*>(a.out)[((row0 + qi) * nq + hq) * VPT + 16 * hh + 4 * g4 + w] = v;
     }
   }
-  if (hq % group == 0) prefill_append<VPT>(a, b, h, p, row0, i0, min(16 * QG, p - i0), tid, 256);
+  if (hq % group == 0) prefill_append<VPT>(a, b, h, p, row0, i0, min(16, p - i0), tid, 256);
 }
 
 // bf16 on the matrix cores, flash-attention style: a workgroup of 4*S waves

@@ -194,12 +194,13 @@ def test_many_holes_rows_of_different_ages(shape):
 
 # The fp32 prefill kernel at the edges of its tiles: prompts of one token, one
 # short of, exactly and one past a 16-key block and a round of the four waves'
-# blocks, several prompts in one step, and enough heads and tiles for 32
-# positions per workgroup (64 heads of 64 and 32 of 128 at 300 tokens); then
-# the same prompt with a value that is not finite near its end, which the
-# positions before it must not see.
+# blocks, several prompts in one step, more workgroups than run at once (64 heads of
+# 64 and 32 of 128 at 300 tokens) and the launch of one workgroup per CU (8 heads of
+# 128 at 601 tokens); then the same prompt with a value that is not finite near its
+# end, which the positions before it must not see.
 @pytest.mark.parametrize("heads,kv,D,lens", [(4, 4, 64, [1, 15, 16, 17]), (4, 2, 128, [63, 64, 65, 2]),
-                                             (8, 1, 64, [33, 130]), (64, 8, 64, [300]), (32, 32, 128, [300, 49])])
+                                             (8, 1, 64, [33, 130]), (64, 8, 64, [300]), (32, 32, 128, [300, 49]),
+                                             (8, 2, 128, [601, 20])])
 def test_f32_prefill_edges(heads, kv, D, lens):
     import torch
     from paper_2410_18701_amd.cache import BatonCache
@@ -238,6 +239,56 @@ def test_f32_prefill_edges(heads, kv, D, lens):
             rows = slice(T - p, T - 1)
             assert (ob[b, rows] - out[b, rows]).abs().max() <= 1e-5 if p > 1 else True
             assert not torch.isfinite(ob[b, T - 1]).any()
+
+
+def _scores_by_four(q, k, scale):
+    """base-2 scores of q [n][D] against k [m][D] in float32 as a lane group adds them: each
+    lane four products in a chain of fused multiply-adds, then a tree over the lanes."""
+    f32 = np.float32
+    qs = (q.astype(f32) * f32(f32(scale) * f32(1.4426950408889634))).astype(f32)
+    n, m, lanes = q.shape[0], k.shape[0], q.shape[1] // 4
+    acc = np.zeros((n, m, lanes), f32)
+    for e in range(4):   # exact products in float64, one rounding per multiply-add
+        acc = (acc + qs[:, None, e::4].astype(np.float64) * k[None, :, e::4].astype(np.float64)).astype(f32)
+    while acc.shape[2] > 1:
+        acc = acc[:, :, 0::2] + acc[:, :, 1::2]
+    return acc[:, :, 0]
+
+
+# fp32 prompts whose rounding error is mostly the scores': no larger against float64
+# than with scores added four products at a time and then as a tree, and the softmax
+# and the products in float32.  With that order the kernel has 0.97 to 1.02 times the
+# reference's error, with chains of four matrix operations 1.15 to 1.22; the bound
+# leaves 3% for the sample (3,800 rows and more, about 1%) and the later sums' order.
+@pytest.mark.parametrize("D,scale,p", [(64, 1.0, 40), (64, 4.0, 100), (128, 1.0, 100), (128, 2.0, 100)])
+def test_f32_prefill_score_rounding(D, scale, p):
+    import torch
+    from paper_2410_18701_amd.cache import BatonCache
+    H, B = 16, 6
+    g = torch.Generator().manual_seed(D + p)
+    q, k, v = (torch.randn((B, p, H, D), generator=g) for _ in range(3))
+    cache = BatonCache(1, B, H, H, D, capacity=p + 64, dtype="f32")
+    cache.shape_insert(list(range(B)), [p] * B)
+    out = torch.empty((B, p, H, D), device="cuda")
+    cache.decode_attn(0, q.cuda(), k.cuda(), v.cuda(), out=out, scale=scale)
+    cache.advance()
+    out = out.cpu().numpy()
+    cache.close()
+    hide = np.triu(np.ones((p, p), bool), 1)
+    err = [0.0, 0.0]
+    for b in range(B):
+        for h in range(H):
+            qh, kh, vh = (x[b, :, h].numpy() for x in (q, k, v))
+            exact = np.where(hide, -np.inf, qh.astype(np.float64) @ kh.astype(np.float64).T * scale)
+            w = np.exp(exact - exact.max(1, keepdims=True))
+            want = w @ vh.astype(np.float64) / w.sum(1, keepdims=True)
+            s = np.where(hide, np.float32(-np.inf), _scores_by_four(qh, kh, scale))
+            w = np.exp2(s - s.max(1, keepdims=True))   # in float32 like what follows
+            err[0] += ((out[b, :, h] - want) ** 2).sum()
+            err[1] += ((w @ vh / w.sum(1, keepdims=True) - want) ** 2).sum()
+    ratio = (err[0] / err[1]) ** 0.5
+    print(f"[f32 score rounding] D {D} scale {scale} p {p}: {ratio:.3f}", flush=True)
+    assert ratio <= 1.05, ratio
 
 
 # The long-prompt bf16 kernel (128 positions per workgroup; the longest prompt times
