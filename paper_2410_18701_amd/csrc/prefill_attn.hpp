@@ -701,6 +701,18 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, uint8_t* ds
 #endif
 }
 
+// This wave's LDS reads and all but its last VM loads have finished, then the
+// barrier.  __syncthreads() does not promise that another wave's loads into LDS
+// have landed.
+template <int VM>
+__device__ __forceinline__ void wait_and_barrier() {
+  static_assert(VM < 16, "vmcnt's low four bits");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070 | VM);       // vmcnt <= VM, lgkmcnt 0
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <int D, int G>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 prefill_fa32_kernel(const PrefillArgs a) {
@@ -841,18 +853,15 @@ prefill_fa32_kernel(const PrefillArgs a) {
         lsum = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pw[r / 8][r % 8], pw[r / 8][r % 8 + 1]}, ones, lsum, false);
       s = sn;
     }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0070 | (2 * NI));   // vmcnt <= 2 NI, lgkmcnt 0
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    wait_and_barrier<2 * NI>();
   };
   fetch(rk, off_k, 0, ldsK0);
   fetch(rk, off_k, 1, ldsK1);
   fetch(rk, off_k, 2, ldsK2);
   fetch(rv, off_v, 0, ldsV0);
-  __syncthreads();
+  wait_and_barrier<0>();
   s = scores(ldsK0);
-  __syncthreads();
+  wait_and_barrier<0>();                         // K block 0 is read: iteration 0 loads over it
   for (int32_t t = 0;; t += 3) {                 // bounds are workgroup-uniform; iteration last_t + 1 is the last
     step(t, ldsK1, ldsV2, ldsK0, ldsV1);
     if (t > last_t) break;
