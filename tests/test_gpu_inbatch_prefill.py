@@ -291,11 +291,34 @@ def test_f32_prefill_score_rounding(D, scale, p):
     assert ratio <= 1.05, ratio
 
 
-# The long-prompt bf16 kernel (128 positions per workgroup; the longest prompt times
-# the workgroups at least 2^20, 2^21 at head_dim 64) at its edges: one token past and one short of a 32-key
-# block, a wave's positions and a tile, prompts of a few tokens beside a long one
-# (tiles of waves with nothing to do), every grouping, both head sizes, a negative
-# scale; against float64 on a few heads, the appended rows bit for bit on all.
+# Bound of a position's outputs against float64, 2-norm over 2-norm: the weights and the
+# outputs are rounded to bf16, 2^-9 each at worst (the kernel's mean is 0.002).  A key
+# too many or too few near position 1,024 is about 0.03, a missing block of 32 keys 0.1.
+POSITION_REL = 6e-3
+
+
+def _check_prompt(out, q, k, v, p, scale, what):
+    """Causal attention outputs out [p][heads][D] of a prompt against float64, on three
+    heads, a position at a time."""
+    import torch
+    heads, kv = q.shape[1], k.shape[1]
+    hide = torch.ones(p, p, dtype=torch.bool).triu(1)
+    for h in (0, heads // 2 - 1, heads - 1):
+        kk, vv = (x[:, h // (heads // kv)].double() for x in (k, v))
+        want = torch.softmax((q[:, h].double() @ kk.T * scale).masked_fill(hide, -np.inf), -1) @ vv
+        err = (out[:, h].double() - want).norm(dim=1) / want.norm(dim=1)
+        assert err.max() <= POSITION_REL, f"{what} head {h} position {int(err.argmax())}: {err.max()}"
+
+
+def _long_prompt_kernel(heads, D, lens):
+    """Whether these prompts take the kernel of 128 positions per workgroup."""
+    return max(lens) >= 512 and sum(-(-p // 128) for p in lens) * heads * max(lens) >= (1 << 21 if D == 64 else 1 << 20)
+
+
+# The long-prompt bf16 kernel (128 positions per workgroup) at its edges: one token past
+# and one short of a 32-key block, a wave's positions and a tile, prompts of a few tokens
+# beside a long one (tiles of waves with nothing to do), every grouping, both head sizes,
+# a negative scale; against float64 on a few heads, the appended rows bit for bit on all.
 @pytest.mark.parametrize("heads,kv,D,lens,scale", [
     (64, 8, 128, [1025, 1, 31, 513], 0.0), (64, 64, 128, [1055, 129, 640], 0.0),
     (64, 16, 64, [1030, 1025, 992, 895], 0.0), (64, 32, 128, [1119, 33, 700], -0.2),
@@ -309,7 +332,7 @@ def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
     for b, p in enumerate(lens):          # positions without a token: not read into a result
         for x in (q, k, v):
             x[b, :T - p] = float("nan")
-    assert sum(-(-p // 128) for p in lens) * heads * T >= (1 << 21 if D == 64 else 1 << 20)
+    assert _long_prompt_kernel(heads, D, lens)
     cache = BatonCache(1, B, heads, kv, D, capacity=T + 64, dtype="bf16")
     cache.shape_insert(list(range(B)), lens)
     out = torch.full((B, T, heads, D), float("nan"), dtype=torch.bfloat16, device="cuda")
@@ -317,15 +340,54 @@ def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
     cache.advance()
     ks, vs = cache.extract(list(range(B)))
     out = out.cpu()
-    sc = scale or D ** -0.5
     for b, p in enumerate(lens):
         assert torch.equal(ks[b][0].cpu(), k[b, T - p:].transpose(0, 1).contiguous()), "appended keys"
         assert torch.equal(vs[b][0].cpu(), v[b, T - p:].transpose(0, 1).contiguous()), "appended values"
         assert torch.isnan(out[b, :T - p]).all(), "a position without a token was written"
-        hide = torch.ones(p, p, dtype=torch.bool).triu(1)
-        for h in (0, heads // 2 - 1, heads - 1):
-            kk, vv = (x[b, T - p:, h // (heads // kv)].double() for x in (k, v))
-            s = (q[b, T - p:, h].double() @ kk.T * sc).masked_fill(hide, -np.inf)
-            err = (out[b, T - p:, h].double() - torch.softmax(s, -1) @ vv).abs().max()
-            assert err <= 2e-2, f"slot {b} head {h}: {err}"
+        _check_prompt(out[b, T - p:], q[b, T - p:], k[b, T - p:], v[b, T - p:], p, scale or D ** -0.5, f"slot {b}")
+    cache.close()
+
+
+# The same kernel in a running batch: two rows decode beside the prompts, and the ring,
+# which a query before them has moved on, ends in the middle of the prompts' columns.
+@pytest.mark.parametrize("heads,kv,D,lens", [(64, 8, 128, [1055, 1030]), (64, 64, 64, [1290, 1313, 900])])
+def test_long_prompts_beside_decoding_rows_over_the_rings_end(heads, kv, D, lens):
+    import torch
+    from paper_2410_18701_amd.cache import BatonCache
+    assert _long_prompt_kernel(heads, D, lens)
+    rows, T, cap = [37, 90], max(lens), max(lens) + 250
+    B = 3 + len(lens)
+    g = torch.Generator().manual_seed(sum(lens))
+    src = [tuple(torch.randn((1, kv, n, D), generator=g).bfloat16() for _ in range(2)) for n in rows]
+    q, k, v = (torch.randn((B, T, h, D), generator=g).bfloat16() for h in (heads, kv, kv))
+    cache = BatonCache(1, B, heads, kv, D, capacity=cap, dtype="bf16")
+    cache.shape_insert([2], [300])
+    cache.decode_attn(0, *(x[:, :300].contiguous().cuda() for x in (q, k, v)))
+    cache.advance()
+    cache.embed([0, 1], rows, [s[0].cuda() for s in src], [s[1].cuda() for s in src])
+    cache.evict([2], release=True)
+    slots = list(range(3, B))
+    cache.shape_insert(slots, lens)
+    L, base, _ = cache.query()
+    first = (base + L) % cap
+    assert L == max(rows) and 0 < first < cap < first + T, (base, L, T, cap)   # the step's columns wrap
+    out = torch.full((B, T, heads, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    cache.decode_attn(0, q.cuda(), k.cuda(), v.cuda(), out=out)
+    cache.advance()
+    out = out.cpu()
+    ks, vs = cache.extract([0, 1] + slots)
+    for b, p in zip(slots, lens):
+        for got, x in ((ks, k), (vs, v)):
+            assert torch.equal(got[b - 1][0].cpu(), x[b, T - p:].transpose(0, 1).contiguous()), "appended rows"
+        assert torch.isnan(out[b, :T - p]).all(), "a position without a token was written"
+        _check_prompt(out[b, T - p:], q[b, T - p:], k[b, T - p:], v[b, T - p:], p, D ** -0.5, f"slot {b}")
+    for b in (0, 1):
+        kk, vv = (torch.cat([src[b][i][0], (k, v)[i][b, 0].unsqueeze(1)], 1) for i in (0, 1))   # [kv][n + 1][D]
+        assert torch.equal(ks[b][0].cpu(), kk) and torch.equal(vs[b][0].cpu(), vv), "the decoding row's tokens"
+        kk, vv = (x.double().repeat_interleave(heads // kv, 0) for x in (kk, vv))
+        s = (q[b, 0].double().unsqueeze(1) @ kk.transpose(1, 2)).squeeze(1) * D ** -0.5
+        want = (torch.softmax(s, -1).unsqueeze(1) @ vv).squeeze(1)
+        err = (out[b, 0].double() - want).norm(dim=1) / want.norm(dim=1)
+        assert err.max() <= POSITION_REL, f"row {b}: {err.max()}"
+        assert torch.isnan(out[b, 1:]).all(), "a position without a token was written"
     cache.close()
