@@ -16,6 +16,7 @@
 #include "kv_ops.hpp"
 #include "layer_ops.hpp"
 #include "prefill_attn.hpp"
+#include "prefill_plan.hpp"
 
 #ifndef BATON_GQA_MFMA
 #define BATON_GQA_MFMA 1   // grouped-query bf16 attention on the matrix cores
@@ -233,17 +234,8 @@ void launch_prefill_g(const baton_cache* c, baton::PrefillArgs& a, hipStream_t s
   int32_t longest = 0;
   for (int32_t i = 0; i < a.n_ins; ++i) longest = std::max(longest, a.plen[i]);
   auto grid = [&] { return dim3((unsigned)((int64_t)a.n_tiles * (c->d.n_q_heads + c->d.n_kv_heads))); };   // and the append workgroups
-  // 128 positions per workgroup and 32 per wave where there are enough
-  // workgroups of long enough prompts: the product of the two decides (its
-  // fewer, longer chains lose where the GPU is not full of them).  64 / 128
-  // positions, us per layer at head_dim 128: 64 heads, 4096 tokens (2048
-  // workgroups) 403 / 322, 2500 (1280) 160 / 140, eight prompts of 512 (2048) 90 /
-  // 82; 32 heads, 2048 tokens (512) 71 / 66, 1500 and 1200 (704) 66 / 60, two of
-  // 1024 (512) 44 / 46.  At head_dim 64 the 64-position kernel runs four
-  // workgroups a CU: 32 heads, 4096 tokens (1024) 117 / 102, 2048 (512) 38 / 39,
-  // four of 1024 (1024) 43 / 49.
   prefill_tiles(c, a, baton::kPrefillTile32);
-  if (longest >= 512 && (int64_t)longest * a.n_attn >= (D == 64 ? 1 << 21 : 1 << 20)) {
+  if (baton::prefill_long(D, a.plen, a.n_ins, a.n_attn)) {
     hipLaunchKernelGGL((baton::prefill_fa32_kernel<D, G>), grid(), dim3(256), 0, s, a);
     return;
   }

@@ -1,5 +1,6 @@
-"""The library's rule for packed products (csrc/gemm_plan.hpp, host code without
-a GPU header), compiled as it stands and called from the tests."""
+"""The library's rules for packed products and for a step's bf16 prompts
+(csrc/gemm_plan.hpp, csrc/prefill_plan.hpp: host code without a GPU header), compiled as
+they stand and called from the tests."""
 import collections
 import ctypes
 import functools
@@ -10,6 +11,7 @@ import tempfile
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_18701_amd", "csrc")
 SHIM = """
 #include "gemm_plan.hpp"
+#include "prefill_plan.hpp"
 extern "C" void plan(int rows, int slices, int in_dim, int gated, int max_splits, int* o) {
   const baton::GemmPlan p = baton::packed_gemm_plan(rows, slices, in_dim, gated != 0, max_splits);
   const int v[] = {p.kind, p.mt, p.ns, p.chunks, p.groups, p.tc, p.splits};
@@ -17,6 +19,9 @@ extern "C" void plan(int rows, int slices, int in_dim, int gated, int max_splits
 }
 extern "C" int tile_built(int mt, int ns, int chunks, int gated) {
   return baton::tile_gemm_built(mt, ns, chunks, gated != 0);
+}
+extern "C" int prefill_long(int head_dim, const int* plen, int n, int wgs) {
+  return baton::prefill_long(head_dim, plen, n, wgs);
 }
 """
 ROW, STAGED, TILE = 0, 1, 2
@@ -69,3 +74,9 @@ def past_64(rows, out_dim, in_dim):
         if (out_dim // 32 if gated else -(-out_dim // 16)) % ((2 if gated else kWaves) * p.ns):
             forms.add((p.mt, p.ns, p.chunks > 1, gated))
     return forms
+
+
+def prefill_long(heads, head_dim, lens):
+    """Whether prompts of these lengths take the kernel of 128 positions per workgroup."""
+    wgs = heads * sum(-(-p // 128) for p in lens)
+    return bool(lib().prefill_long(head_dim, (ctypes.c_int * len(lens))(*lens), len(lens), wgs))

@@ -10,6 +10,7 @@ import os
 import numpy as np
 import pytest
 
+from tests import gemm_plan as G
 from tests import oracle_pins, parity
 
 pytestmark = pytest.mark.gpu
@@ -310,11 +311,6 @@ def _check_prompt(out, q, k, v, p, scale, what):
         assert err.max() <= POSITION_REL, f"{what} head {h} position {int(err.argmax())}: {err.max()}"
 
 
-def _long_prompt_kernel(heads, D, lens):
-    """Whether these prompts take the kernel of 128 positions per workgroup."""
-    return max(lens) >= 512 and sum(-(-p // 128) for p in lens) * heads * max(lens) >= (1 << 21 if D == 64 else 1 << 20)
-
-
 # The long-prompt bf16 kernel (128 positions per workgroup) at its edges: one token past
 # and one short of a 32-key block, a wave's positions and a tile, prompts of a few tokens
 # beside a long one (tiles of waves with nothing to do), every grouping, both head sizes,
@@ -332,7 +328,7 @@ def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
     for b, p in enumerate(lens):          # positions without a token: not read into a result
         for x in (q, k, v):
             x[b, :T - p] = float("nan")
-    assert _long_prompt_kernel(heads, D, lens)
+    assert G.prefill_long(heads, D, lens)
     cache = BatonCache(1, B, heads, kv, D, capacity=T + 64, dtype="bf16")
     cache.shape_insert(list(range(B)), lens)
     out = torch.full((B, T, heads, D), float("nan"), dtype=torch.bfloat16, device="cuda")
@@ -354,7 +350,7 @@ def test_long_prompt_kernel_edges(heads, kv, D, lens, scale):
 def test_long_prompts_beside_decoding_rows_over_the_rings_end(heads, kv, D, lens):
     import torch
     from paper_2410_18701_amd.cache import BatonCache
-    assert _long_prompt_kernel(heads, D, lens)
+    assert G.prefill_long(heads, D, lens)
     rows, T, cap = [37, 90], max(lens), max(lens) + 250
     B = 3 + len(lens)
     g = torch.Generator().manual_seed(sum(lens))
