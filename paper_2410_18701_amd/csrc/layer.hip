@@ -99,6 +99,16 @@ int32_t launch_packed_gemm(baton::GemmArgs& a, int32_t max_splits, hipStream_t s
   return built ? p.splits : 0;
 }
 
+void launch_rmsnorm(const void* x, const void* gain, void* y, int32_t rows, int32_t dim, float eps, hipStream_t s) {
+  auto launch = [&](auto kernel, int32_t threads) {
+    hipLaunchKernelGGL(kernel, dim3(rows), dim3(threads), 0, s, static_cast<const baton::u32x4*>(x),
+                       static_cast<const baton::u32x4*>(gain), static_cast<baton::u32x4*>(y), dim / 8, 1.0f / dim, eps);
+  };
+  static_assert(baton::kRowThreads == 512, "norm_threads' larger choice");
+  if (baton::norm_threads(rows, dim) == 256) launch(baton::rmsnorm_kernel<256>, 256);
+  else launch(baton::rmsnorm_kernel<baton::kRowThreads>, baton::kRowThreads);
+}
+
 }  // namespace
 
 extern "C" {
@@ -164,9 +174,7 @@ baton_status linear_packed(int32_t dtype, const void* x, const void* wp, void* y
       hipLaunchKernelGGL(baton::gemm_reduce_kernel, dim3((unsigned)((n_out / 4 + 255) / 256)), dim3(256), 0, stream,
                          a.part, a.y, S, n_out, accumulate);
     if (gain)
-      hipLaunchKernelGGL(baton::rmsnorm_kernel, dim3(rows), dim3(baton::kRowThreads), 0, stream,
-                         static_cast<const baton::u32x4*>(y), static_cast<const baton::u32x4*>(gain),
-                         static_cast<baton::u32x4*>(y_norm), out_dim / 8, 1.0f / out_dim, eps);
+      launch_rmsnorm(y, gain, y_norm, rows, out_dim, eps, stream);
   }
   return hipGetLastError() == hipSuccess ? BATON_OK : BATON_EHIP;
 }
@@ -216,9 +224,7 @@ baton_status baton_rmsnorm(int32_t dtype, const void* x, const void* gain, void*
   if (!x || !gain || !y || rows < 1 || dim < 8 || dim % 8 || !(eps >= 0.f) || !std::isfinite(eps)) return BATON_EINVAL;
   if (dtype != BATON_BF16) return BATON_EDTYPE;
   if (!aligned16(x) || !aligned16(gain) || !aligned16(y)) return BATON_EINVAL;
-  hipLaunchKernelGGL(baton::rmsnorm_kernel, dim3(rows), dim3(baton::kRowThreads), 0, stream,
-                     static_cast<const baton::u32x4*>(x), static_cast<const baton::u32x4*>(gain),
-                     static_cast<baton::u32x4*>(y), dim / 8, 1.0f / dim, eps);
+  launch_rmsnorm(x, gain, y, rows, dim, eps, stream);
   return hipGetLastError() == hipSuccess ? BATON_OK : BATON_EHIP;
 }
 

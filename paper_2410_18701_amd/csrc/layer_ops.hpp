@@ -15,24 +15,26 @@ namespace {   // internal linkage: the kernels are included by two translation u
 // registers for the second pass.  Against 256
 // threads reading twice, whole llama2-7b layers: 585.0 -> 580.0 us for two at 64
 // rows, 206.9 -> 203.5 at one; the feed-forward block at 256 rows 113.9 -> 110.3.
+// (rmsnorm_kernel alone takes 256 for many short rows, norm_threads.)
 constexpr int kRowThreads = 512;
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
 }
 
-// y[r] = x[r] / sqrt(mean(x[r]^2) + eps) * g, one workgroup per row; dim a
-// multiple of 8 (16-byte vectors).
-__global__ void __launch_bounds__(kRowThreads) rmsnorm_kernel(const u32x4* __restrict__ x,
-                                                              const u32x4* __restrict__ g,
-                                                              u32x4* __restrict__ y, int32_t vec_per_row,
-                                                              float inv_dim, float eps) {
-  __shared__ float part[kRowThreads / kWave];
+// y[r] = x[r] / sqrt(mean(x[r]^2) + eps) * g, one workgroup of NT threads per
+// row; dim a multiple of 8 (16-byte vectors).  Rows of at most 256 vectors have
+// the same bits with 256 threads as with more, whose sums are zeros.
+template <int NT>
+__global__ void __launch_bounds__(NT) rmsnorm_kernel(const u32x4* __restrict__ x, const u32x4* __restrict__ g,
+                                                     u32x4* __restrict__ y, int32_t vec_per_row, float inv_dim,
+                                                     float eps) {
+  __shared__ float part[NT / kWave];
   const int64_t row = blockIdx.x;
   const u32x4* xr = x + row * vec_per_row;
   float ss = 0.f;
   u32x4 w0 = {0, 0, 0, 0};   // the thread's first vector
-  for (int i = threadIdx.x; i < vec_per_row; i += kRowThreads) {
+  for (int i = threadIdx.x; i < vec_per_row; i += NT) {
     const u32x4 w = xr[i];
     if (i == (int)threadIdx.x) w0 = w;
 #pragma unroll
@@ -47,9 +49,9 @@ __global__ void __launch_bounds__(kRowThreads) rmsnorm_kernel(const u32x4* __res
   __syncthreads();
   float tot = 0.f;
 #pragma unroll
-  for (int w = 0; w < kRowThreads / kWave; ++w) tot += part[w];
+  for (int w = 0; w < NT / kWave; ++w) tot += part[w];
   const float inv = 1.0f / sqrtf(tot * inv_dim + eps);
-  for (int i = threadIdx.x; i < vec_per_row; i += kRowThreads) {
+  for (int i = threadIdx.x; i < vec_per_row; i += NT) {
     const u32x4 w = i == (int)threadIdx.x ? w0 : xr[i], gw = g[i];
     u32x4 o;
 #pragma unroll

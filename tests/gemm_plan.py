@@ -20,6 +20,7 @@ extern "C" void plan(int rows, int slices, int in_dim, int gated, int max_splits
 extern "C" int tile_built(int mt, int ns, int chunks, int gated) {
   return baton::tile_gemm_built(mt, ns, chunks, gated != 0);
 }
+extern "C" int norm_threads(int rows, int dim) { return baton::norm_threads(rows, dim); }
 extern "C" int prefill_long(int head_dim, const int* plen, int n, int wgs) {
   return baton::prefill_long(head_dim, plen, n, wgs);
 }

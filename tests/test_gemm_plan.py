@@ -96,3 +96,11 @@ def test_launches_stay_below_2_to_the_32_threads():
                 for gated in (False, True):
                     p = G.plan(rows, out_dim, in_dim, gated)
                     assert p.groups * p.chunks * p.splits * 256 < 1 << 32, (rows, out_dim, in_dim, gated, p)
+
+
+@pytest.mark.parametrize("rows,dim,threads", [
+    (4096, 512, 256), (1024, 2048, 256), (16384, 64, 256), (513, 1024, 256), (512, 512, 512), (64, 2048, 512),
+    (256, 512, 512), (4096, 4096, 512), (1, 64, 512)])
+def test_norm_threads(rows, dim, threads):
+    """512 threads took up to 1.45 times the time over many short rows."""
+    assert G.lib().norm_threads(rows, dim) == threads

@@ -305,6 +305,19 @@ def test_rmsnorm_and_silu_mul():
     _close(_val(out), LL.silu(gu[:, :11008]) * gu[:, 11008:], atol=1e-6, what="silu_mul")
 
 
+@pytest.mark.parametrize("rows,dim", [(513, 8), (600, 520), (1030, 2048), (520, 2056)])
+def test_rmsnorm_of_many_rows(rows, dim):
+    """More rows than a decode step has (another workgroup size up to 2048 elements): the
+    oracle's values, and each row's bits do not depend on how many there are."""
+    rng = np.random.default_rng(rows + dim)
+    xb, gb = _bits(rng, (rows, dim)), _bits(rng, (dim,))
+    y, y8 = (torch.full((n, dim), float("nan"), dtype=torch.bfloat16, device="cuda") for n in (rows, 8))
+    PL.rmsnorm(_dev(xb), _dev(gb), y, 1e-5)
+    PL.rmsnorm(_dev(xb[:8]), _dev(gb), y8, 1e-5)
+    _close(_val(y), LL.rmsnorm(O.widen(xb, O.BF16), O.widen(gb, O.BF16), 1e-5), atol=1e-6, what="rmsnorm")
+    assert np.array_equal(parity.host_bits(y8), parity.host_bits(y)[:8])
+
+
 def test_rope_at_token_counts():
     """Positions are the slots' token counts: holes from an in-batch prefill
     do not count, free slots are rotated at 0."""
