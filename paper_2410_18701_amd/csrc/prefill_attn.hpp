@@ -596,9 +596,8 @@ prefill_fa_kernel(const PrefillArgs a) {
 
 // bf16 for long prompts, on v_mfma_f32_32x32x16_bf16: four waves of 32 prompt
 // positions of one query head, the keys in blocks of 32.  In the kernel above
-// every 32 x 16 block of scores reads its 16 KB of keys and values from LDS (73%
-// of the LDS's rate at 4096 tokens); here the same 16 KB serve 32 positions, the
-// loads go to LDS without registers two blocks ahead, and the block loop is
+// every 32 x 16 block of scores reads its 16 KB of keys and values from LDS; here
+// the same 16 KB serve 32 positions, the loads go to LDS without registers two blocks ahead, and the block loop is
 // pipelined in software so that a wave's matrix and vector work overlap:
 // iteration t multiplies the values of block t - 1 and takes the maximum of block
 // t's scores, then computes the scores of block t + 1 and the weights of block t.
@@ -610,9 +609,11 @@ prefill_fa_kernel(const PrefillArgs a) {
 //  * the weights' sum is of the bf16 weights P.V is made of.
 // 64 query heads over 8 kv-heads of 128, 4096 tokens: 390 -> 325 us (0.70 -> 0.85
 // PFLOP/s over the visible pairs).  What bounds it now: two waves per SIMD (173
-// registers) that wait for their own chain a third of the time, and the clock,
-// about 1.9 GHz under this load; capped for three waves it spills, and two
-// accumulators per score or a raised wave priority changed nothing.
+// registers) that wait for their own chain 0.34 of their cycles (the matrix cores
+// busy 0.46 of the time, no LDS conflicts), and the clock, 1.88 GHz under this
+// load; before its first block each wave also waits for its query fragments, whose
+// loads the compiler takes one after the other.  Capped for three waves it spills,
+// and two accumulators per score or a raised wave priority changed nothing.
 constexpr int kPrefillTile32 = 128;
 // How far (base 2) a block's maximum may pass the reference before it moves.
 // The weight of the key a reference was taken from is exactly 1; the further a
