@@ -379,9 +379,9 @@ baton_status baton_set_split_tokens(baton_cache* cache, int32_t tokens);
  * decode step's batch) on the library's weight-streaming kernel, which reads
  * the weight in a packed form made once per weight by baton_linear_pack.  The
  * weight dominates the traffic of such a product and is read about once from
- * HBM (past 128 rows they are taken in two chunks by workgroups dealt to the
- * same XCD one after the other, the second finding the weight in that XCD's
- * L2); the packed form lets each wave stream it in contiguous 1 KB blocks.
+ * HBM (past 64 rows they may be taken in chunks of 48 to 128 by workgroups
+ * dealt to the same XCD one after the other, all but the first finding the
+ * weight in that XCD's L2); the packed form lets each wave stream it in contiguous 1 KB blocks.
  *
  * baton_linear_packed_bytes: bytes of the packed form of an [out_dim][in_dim]
  * weight: 2 * ceil(out_dim / 16) * 16 * ceil(in_dim / 32) * 32 (0 for sizes < 1).

@@ -389,10 +389,11 @@ __device__ __forceinline__ bool gemm_tile(const GemmArgs& a, int32_t& grp, int32
 // activations shared through LDS, each wave's weights straight to registers.
 // Per 64-wide step a workgroup brings 2 MT KB of activations and 8 NS KB of
 // weights into its CU for 2 MT NS matrix operations per wave; a CU takes about
-// 25 bytes a clock of this mix whatever the pipeline (measured with register-
-// and LDS-direct-staged activations, one and two waves per SIMD: the same
-// times), so what counts is the bytes per operation: as many slices per wave
-// as still give every CU a workgroup.  Both staging and fragments run ahead:
+// 64 bytes of activations and 73 of weights per ns (the fit in gemm_plan.hpp)
+// whatever the pipeline (register- and LDS-direct-staged activations, one and
+// two waves per SIMD: the same times), so what counts is the bytes per
+// operation: tiles as large as still give every CU a workgroup.  Both staging
+// and fragments run ahead:
 //  * three LDS buffers, one barrier per step: while step b is multiplied, step
 //    b + 2's activations go from registers to LDS, and step b + 1's first
 //    fragments are read from the buffer that the last barrier completed;
