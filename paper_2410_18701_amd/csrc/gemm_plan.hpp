@@ -200,7 +200,9 @@ inline GemmPlan packed_gemm_plan(int32_t rows, int32_t slices, int32_t in_dim, b
 // one round, but where rows fill the GPU and leave half of them idle 256 let more
 // rows run at once.  512 / 256 threads, us: 1024 rows of 2048 3.79 / 3.71, of 512
 // 3.09 / 2.89, 16,384 of 512 15.2 / 11.0, of 2048 26.4 / 23.4; but 256 rows of 2048
-// 2.83 / 2.90, 1024 of 4096 5.00 / 5.13.
-inline int32_t norm_threads(int32_t rows, int32_t dim) { return rows > 512 && dim <= 2048 ? 256 : 512; }
+// 2.83 / 2.90, 1024 of 4096 5.00 / 5.13.  And a launch has less than 2^32 threads.
+inline int32_t norm_threads(int32_t rows, int32_t dim) {
+  return rows > 512 && (dim <= 2048 || rows >= 1 << 23) ? 256 : 512;
+}
 
 }  // namespace baton

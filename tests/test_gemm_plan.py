@@ -104,3 +104,9 @@ def test_launches_stay_below_2_to_the_32_threads():
 def test_norm_threads(rows, dim, threads):
     """512 threads took up to 1.45 times the time over many short rows."""
     assert G.lib().norm_threads(rows, dim) == threads
+
+
+@pytest.mark.parametrize("rows", [(1 << 23) - 1, 1 << 23, (1 << 24) - 1])
+@pytest.mark.parametrize("dim", [8, 2048, 2056, 4096])
+def test_norm_launches_fit(rows, dim):
+    assert rows * G.lib().norm_threads(rows, dim) < 1 << 32
