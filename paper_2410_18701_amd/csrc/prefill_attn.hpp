@@ -326,9 +326,10 @@ prefill_f32_kernel(const PrefillArgs a) {
 // walking every S-th tile of KT keys (S tiles staged in LDS per iteration, K
 // and V both as rows, 16-byte stores), and the quartets' softmax states merge
 // through LDS at the end -- S shortens the longest causal tile's chain of
-// iterations.  With long prompts the kernel's limit is the LDS read bandwidth:
-// each 32-key block costs a wave 16 KB of LDS reads, as many bytes as its matrix
-// operations take cycles (prefill_fa32_kernel halves that).
+// iterations.  What bounds it is that chain: the waves wait 0.58 of their cycles
+// (prompts of 64 to 1,018 tokens, 32 heads of 128) on the staging and its barriers
+// and on the dependent products and softmax steps.  Each 32-key block costs a
+// wave 16 KB of LDS reads (prefill_fa32_kernel halves that per position).
 //  * QK^T: A = 16 key rows (lane l: key l % 16 of the half tile), B = 16 of
 //    the wave's positions; the score of key 4*(l/16) + r (first 16 keys) and
 //    16 + 4*(l/16) + r (next 16) for position l % 16 lands in
